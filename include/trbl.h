@@ -147,13 +147,14 @@ int trbl_random_tbme(const trbl_orbit* orbits, int n_orbits, uint64_t seed, doub
 
 /* Set H = sum_a e_a n_a + two-body (Sec. 2). spe_p, spe_n: one energy per orbit (host).
    tbme: n_v host elements. Copies everything, builds the one-body jump and
-   identical-particle tables of App. B on the device. Where it fits in a quarter of the free
-   device memory (and below 4 GiB for two species), and for two species where a core pair
-   carries on average at least 16 source pairs (pf-shell spaces; not sd), it also builds the
-   core-pair blocks of the matrix-core products and their slot buffer, which the model keeps:
-   n_prot * n_neut * D * 16 doubles for the pn part of two species, and
-   C(n, 2) * D * 8 doubles for n nucleons of one species. Setting TRBL_PN_TILES=0 in the
-   environment before this call keeps the jump-list and per-element kernels only. */
+   identical-particle tables of App. B on the device. For single-species spaces whose slots fit
+   in a quarter of the free device memory, and for two species where a core pair carries enough
+   source pairs (pf-shell spaces, sd shell up to 4+4), it also builds the core-pair blocks of the
+   matrix-core products and their slot buffers, which the model keeps: for two species
+   n_prot * n_neut * D * 128 bytes where that is below 4 GiB and a quarter of the free memory,
+   else two buffers of 512 MiB, and C(n, 2) * D * 8 doubles for n nucleons of one species. Setting
+   TRBL_PN_TILES=0 in the environment before this call keeps the jump-list and per-element kernels
+   only. */
 int trbl_set_hamiltonian(trbl_model* m, const double* spe_p, const double* spe_n, const trbl_tbme* tbme,
                          int64_t n_v);
 

@@ -188,34 +188,36 @@ static void run_hv(const Model& m, int nb, const void* V, int64_t ldv, void* W, 
   a.citem0 = P.citem0.as<int64_t>();
   // with the pair-block tables the rows and columns kernels write the identical-particle parts and
   // the pair blocks add the pn part
-  // The pair blocks work on 16-column tiles, so narrow products cost nearly as much as 16
-  // columns; below the measured crossover (pf 4+4: FP64 from 5 columns, FP32 from 9, or from 5 at
-  // widths that are not a power of two, where the jump-list kernel stages rows without the DMA)
-  // the jump-list kernel runs instead. TRBL_PN_TILES=2 at set-up takes the pair blocks at every width.
-  const bool pow2 = (nb & (nb - 1)) == 0;
-  const bool wide = sizeof(T) == 8 ? nb >= 5 : (nb >= 9 || (nb >= 5 && !pow2));
-  bool own = m.pn.on && (wide || m.pn.force) && (double)m.dim * (double)ldv * sizeof(T) < 4294967296.0;
-  for (const auto& B : P.bins) own = own && B->mp == 1;
+  const bool own = m.pn.on && !(m.pn.one_tile && nb * sizeof(T) > 128) && ldv * (int64_t)sizeof(T) < ((int64_t)1 << 32);
   a.own = own ? 1 : 0;
   if (!own) {
     dispatch_hv<T>(a, P, s, 3, ~0u);
     return;
   }
-  // With the pair blocks: the columns kernel writes the pp part into W on the model's side stream
-  // while the pair-block kernel writes the pn slots; the own-row kernel then adds the nn part and,
-  // when one 16-column tile covers the product, the slots; a wider product adds its slots in a
-  // pass of its own at the end.
   const PNTiles& pn = m.pn;
+  if (pn.batches.size() > 1) {
+    // the identical-particle parts first; the batches of pair blocks then add to W
+    dispatch_hv<T>(a, P, s, 3, ~0u);
+    launch_pn_tiles<T>(m, nb, static_cast<const T*>(V), ldv, static_cast<T*>(W), ldw, s, true);
+    return;
+  }
+  // One batch: the columns kernel writes the pp part into W on the model's side stream
+  // while the pair-block kernel writes the pn slots; the own-row kernel then adds the nn part and,
+  // when one column tile covers the product, the slots; a wider product adds its slots in a
+  // pass of its own at the end.
   TRBL_HIP(hipEventRecord(pn.ev[0], s));
   TRBL_HIP(hipStreamWaitEvent(pn.side, pn.ev[0], 0));
   a.ppset = 1;
   dispatch_hv<T>(a, P, pn.side, 2, ~0u);
   TRBL_HIP(hipEventRecord(pn.ev[1], pn.side));
-  const bool fused = P.C == 16 && nb <= 16;
+  bool fused = P.ntile == 1;
+  for (const auto& B : P.bins) fused = fused && B->mp == 1 && B->nchunk == 1;  // the whole row in one workgroup
   if (fused) {
     launch_pn_tiles<T>(m, nb, static_cast<const T*>(V), ldv, static_cast<T*>(W), ldw, s, false);
-    a.zs = pn.S;
-    a.zstride = m.dim * 16;
+    a.zs = m.n_prot * m.n_neut;
+    a.zc = pn_slot_chunks(sizeof(T), nb);
+    a.zl = pn_slot_stride(sizeof(T), nb);
+    a.zstride = m.dim;
     a.zbuf = pn.z.p;
   }
   // the own-row bins write disjoint rows: the largest runs here, the others on the side stream

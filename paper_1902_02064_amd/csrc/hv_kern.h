@@ -42,10 +42,12 @@ struct HVArgs {
   int C, ntile, nchunk;  // column tile width, column tiles, target chunks per row/column
   int dma;               // source rows copied by global->LDS DMA (16-byte aligned rows)
   int own;               // identical-particle parts only (the pn part is added by the pair blocks)
-  int zs;                // own-row kernel: slots of the pair-block buffer summed into W (0: none)
+  int mp;                // own-row kernel: targets per lane
+  int zs;                // own-row kernel: slots of a target summed into W (0: none)
+  int zc, zl;            // 16-byte chunks of a slot row: with valid columns, and as laid out
   int ppset;             // columns kernel writes W (instead of adding to it); the own-row kernel then adds
-  int64_t zstride;       // elements between slots of that buffer ([slot][D][16] values of type T)
-  const void* zbuf;
+  int64_t zstride;       // slot rows between slots
+  const void* zbuf;      // slot rows, [slot][D]
   int64_t nn_total;
   const int* blk_dp;
   const int* blk_dn;
@@ -546,9 +548,12 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
 
 // Own-row kernel: the neutron-neutron part and the diagonal of the rows kernel without its pn part,
 // for products whose pn part comes from the pair blocks. One workgroup per target proton row
-// (and column tile); the row is staged once in LDS (dynamic size: the widest sector of the bin).
-template <class T, int C, int NTB, bool DMA>
-__global__ __launch_bounds__(NTB) void hv_own_kernel(HVArgs<T> a) {
+// (and column tile); the row is staged once in LDS (dynamic size: the widest sector of the bin), and
+// each lane serves one target of it, or with MANY a.mp targets one after the other. With a.zs the kernel
+// also sums the pair blocks' slots (one target per lane). Two 768-wide workgroups share a CU (72 KB rows)
+// only below 86 registers a lane, so the compiler is held to 6 wavefronts per SIMD.
+template <class T, int C, int NTB, bool DMA, bool MANY>
+__global__ __launch_bounds__(NTB, NTB == 1024 ? 4 : 6) void hv_own_kernel(HVArgs<T> a) {
   using L = Tile<T, C>;
   extern __shared__ __align__(256) char B0[];
   const int64_t nitems = a.bin_item0[a.bin_nblk];
@@ -566,34 +571,34 @@ __global__ __launch_bounds__(NTB) void hv_own_kernel(HVArgs<T> a) {
   const int dn = a.blk_dn[b];
   const int64_t off = a.blk_off[b];
   const int gn0 = a.blk_n0[b];
-  const int tlo = tc * nthr;
+  const int tlo = tc * nthr * (MANY ? a.mp : 1);
   if (tlo >= dn) return;
   const T* src = a.V + (off + (int64_t)pl * dn) * a.ldv + c0;
   if constexpr (DMA) stage_dma<T, C>(B0, src, a.ldv, dn);
   else stage_sync<T, C>(B0, src, a.ldv, dn, cvalid);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  const int ln = tlo + tid;
-  const bool live = ln < dn;
-  T acc[C];
+  for (int q = 0; q < (MANY ? a.mp : 1); q++) {
+    const int ln = tlo + q * nthr + tid;
+    const bool live = ln < dn;
+    T acc[C];
 #pragma unroll
-  for (int c = 0; c < C; c++) acc[c] = T(0);
-  const int sl = a.blk_nslice0[b] + min(ln, dn - 1) / 64, lo = ln % 64;
-  const int base = a.ne_off[sl], wd = live ? a.ne_w[sl] : 0;
-  for (int k = 0; k < wd; k += 4) {
-    int cc[4];
-    T vv[4];
+    for (int c = 0; c < C; c++) acc[c] = T(0);
+    const int sl = a.blk_nslice0[b] + min(ln, dn - 1) / 64, lo = ln % 64;
+    const int base = a.ne_off[sl], wd = live ? a.ne_w[sl] : 0;
+    for (int k = 0; k < wd; k += 4) {
+      int cc[4];
+      T vv[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const int at = base + (k + u) * 64 + lo;
-      cc[u] = k + u < wd ? a.ne_col[at] : 0;
-      vv[u] = k + u < wd ? a.ne_val[at] : T(0);
+      for (int u = 0; u < 4; u++) {
+        const int at = base + (k + u) * 64 + lo;
+        cc[u] = k + u < wd ? a.ne_col[at] : 0;
+        vv[u] = k + u < wd ? a.ne_val[at] : T(0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; u++) gather_row<T, C>(acc, vv[u], B0, cc[u] * L::RB);
     }
-#pragma unroll
-    for (int u = 0; u < 4; u++) gather_row<T, C>(acc, vv[u], B0, cc[u] * L::RB);
-  }
-  if constexpr (C == 16) {
-    if (a.zs > 0) {
+    if (!MANY && a.zs > 0) {
       // the pn part from the pair-block slots: park the rows in LDS (target order), then stream the
       // slots of the proton row's dn targets in address order and write W once
       __syncthreads();  // every lane has read its staged source rows
@@ -609,36 +614,39 @@ __global__ __launch_bounds__(NTB) void hv_own_kernel(HVArgs<T> a) {
       __syncthreads();
       typedef T zv __attribute__((ext_vector_type(L::VPC)));  // one 16-byte chunk
       const int64_t r0 = off + (int64_t)pl * dn;
-      const int lo_t = tlo, hi_t = min(dn, tlo + nthr);
-      for (int e = lo_t * L::CPR + tid; e < hi_t * L::CPR; e += nthr) {
-        const int t = e / L::CPR, k = e % L::CPR;
+      const zv* zb = static_cast<const zv*>(a.zbuf) + r0 * a.zl;
+      const int64_t step = a.zstride * a.zl;
+      const int hi_t = min(dn, tlo + nthr);
+      for (int e = tlo * a.zc + tid; e < hi_t * a.zc; e += nthr) {
+        const int t = e / a.zc, k = e - t * a.zc;
         zv v = *reinterpret_cast<const zv*>(B0 + L::at(t, k));
-        const T* z = static_cast<const T*>(a.zbuf) + (r0 + t) * 16 + L::VPC * k;
-        int q = 0;
-        for (; q + 8 <= a.zs; q += 8) {  // eight slots in flight, summed in slot order
+        const zv* z = zb + t * a.zl + k;
+        int m = 0;
+        for (; m + 8 <= a.zs; m += 8) {  // eight slots in flight, summed in slot order
           zv zq[8];
 #pragma unroll
-          for (int j = 0; j < 8; j++) zq[j] = __builtin_nontemporal_load(reinterpret_cast<const zv*>(z + (q + j) * a.zstride));
+          for (int u = 0; u < 8; u++) zq[u] = __builtin_nontemporal_load(z + (m + u) * step);
 #pragma unroll
-          for (int j = 0; j < 8; j++) v += zq[j];
+          for (int u = 0; u < 8; u++) v += zq[u];
         }
-        for (; q < a.zs; q++) v += __builtin_nontemporal_load(reinterpret_cast<const zv*>(z + q * a.zstride));
+        for (; m < a.zs; m++) v += __builtin_nontemporal_load(z + m * step);
         T* w = a.W + (r0 + t) * a.ldw + c0 + L::VPC * k;
 #pragma unroll
-        for (int j = 0; j < L::VPC; j++)
-          if (L::VPC * k + j < cvalid) w[j] = a.ppset ? w[j] + v[j] : v[j];
+        for (int u = 0; u < L::VPC; u++)
+          if (L::VPC * k + u < cvalid) w[u] = a.ppset ? w[u] + v[u] : v[u];
       }
       return;
     }
-  }
-  if (!live) return;
-  T* w = a.W + (off + (int64_t)pl * dn + a.nlane[gn0 + ln]) * a.ldw + c0;
+    if (!live) continue;
+    T* w = a.W + (off + (int64_t)pl * dn + a.nlane[gn0 + ln]) * a.ldw + c0;
 #pragma unroll
-  for (int t = 0; t < L::CPR; t++) {
-    const int k = t ^ L::rot();
+    for (int t = 0; t < L::CPR; t++) {
+      const int k = t ^ L::rot();
 #pragma unroll
-    for (int v = 0; v < L::VPC; v++)
-      if (k * L::VPC + v < cvalid) w[k * L::VPC + v] = a.ppset ? w[k * L::VPC + v] + acc[t * L::VPC + v] : acc[t * L::VPC + v];
+      for (int v = 0; v < L::VPC; v++)
+        if (k * L::VPC + v < cvalid)
+          w[k * L::VPC + v] = a.ppset ? w[k * L::VPC + v] + acc[t * L::VPC + v] : acc[t * L::VPC + v];
+    }
   }
 }
 
@@ -729,8 +737,13 @@ template <class T, int C, int NTB>
 static void launch_own(const HVArgs<T>& a, const HVBin& B, hipStream_t s) {
   const dim3 grid((unsigned)((B.items + 7) / 8 * 8)), block(B.nthr);
   const size_t shm = (size_t)B.maxdn * C * sizeof(T);
-  if (a.dma) hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, true>), grid, block, shm, s, a);
-  else hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, false>), grid, block, shm, s, a);
+  if (B.mp > 1) {
+    if (a.dma) hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, true, true>), grid, block, shm, s, a);
+    else hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, false, true>), grid, block, shm, s, a);
+  } else {
+    if (a.dma) hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, true, false>), grid, block, shm, s, a);
+    else hipLaunchKernelGGL((hv_own_kernel<T, C, NTB, false, false>), grid, block, shm, s, a);
+  }
 }
 
 template <class T, int C>
@@ -744,7 +757,8 @@ static void dispatch_c(HVArgs<T>& a, const HVPlan& P, hipStream_t s, int parts, 
     a.bin_item0 = B.item0.as<int64_t>();
     a.bin_nblk = B.nblk;
     if (a.own) {
-      TRBL_REQUIRE(B.mp == 1, TRBL_E_INVALID, "own-row plan with several targets per lane");
+      TRBL_REQUIRE(B.mp == 1 || a.zs == 0, TRBL_E_INVALID, "slot sum with several targets per lane");
+      a.mp = B.mp;
       if (B.ntb == 256) launch_own<T, C, 256>(a, B, s);
       else if (B.ntb == 768) launch_own<T, C, 768>(a, B, s);
       else launch_own<T, C, 1024>(a, B, s);

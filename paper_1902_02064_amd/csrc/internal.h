@@ -156,20 +156,28 @@ struct HVPlan {
 // of the symmetric block H_M[(x,u)][(y,v)] restricted to the pairs outside the cores.
 struct PNTiles {
   bool on = false;
-  bool force = false;        // at every product width (TRBL_PN_TILES=2), not only the wide ones
-  int S = 0;                 // contribution slots per basis state: n_prot * n_neut
-  int nk = 0;                // pair blocks (2M of a pair from -2 tjmax to 2 tjmax)
-  int nrect = 0;             // core-group rectangles (fixed core 2M and parity on both sides)
-  int ncore[2] = {0, 0};
+  bool force = false;        // in every space that allows them (TRBL_PN_TILES=2)
+  bool one_tile = false;     // only for products of one column tile (128-byte rows)
   int max_pairs = 0;         // widest pair block
-  int tpb = 256;             // most core pairs of one work item
-  int64_t items = 0;         // workgroups of one launch
-  DevBuf cw[2], rk[2];       // core words; [core * ns + state]: position of state << 24 | local index of core + state, -1 inside
+  DevBuf rk[2];              // [core * ns + state]: position of state << 24 | local index of core + state, -1 inside
   DevBuf pr_off, pr_xu;      // pair blocks: x | u << 8
   DevBuf hb_off, hb, hb32;   // per pair block: D2 x D2 matrix (FP64, FP32), row = target pair
-  DevBuf rect, rblk, item0;  // rectangles (pair block, rblk start), per rectangle and pair the target block
-                             // (-1: none), work items (rectangle, proton core, first neutron core, count)
+  DevBuf rect, rblk;         // rectangles (pair block, rblk start), per rectangle and pair the target block << 1 |
+                             // parity of its neutron sector (-1: none)
+  DevBuf items;              // work items, batch by batch (rectangle, proton core, first neutron core, count)
   DevBuf boff;               // block offsets as 32-bit integers
+  // Slots. A batch is a run of proton cores; it owns the slot rows [core][x][neutron parity][position
+  // of u][target neutron]. zoff: first slot row of (core, x, neutron parity) inside its batch.
+  struct Batch {
+    int item0, nitems;       // work items
+    int row0, nrows, maxdn;  // target rows it contributes to, the widest of them
+  };
+  std::vector<Batch> batches;
+  int nbuf = 1;              // slot buffers: one batch, or two that alternate
+  int64_t buf_rows = 0;      // slot rows of one buffer
+  int zstep = 0;             // slot rows between positions of u (0: the neutron states of the target's sector)
+  DevBuf zoff;
+  DevBuf trow, tent;         // target rows (first W row, neutron states, first entry, entries) and their slot rows
   hipStream_t side = nullptr;  // the columns kernel and the smaller own-row bins run here
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   PNTiles() = default;
@@ -180,7 +188,7 @@ struct PNTiles {
       if (e) (void)hipEventDestroy(e);
     if (side) (void)hipStreamDestroy(side);
   }
-  DevBuf z;                  // slot buffer [S][D][16] of one 16-column tile (FP64, or FP32 in its first half)
+  DevBuf z;                  // slot buffers (rows of at most 128 bytes: 16 FP64 or 32 FP32 columns)
 };
 
 // The identical-particle part of a single-species space as dense pair blocks (pntile.hip): cores
@@ -258,12 +266,22 @@ void launch_fly(const Model& m, int precision, int nb, const void* V, int64_t ld
                 hipStream_t s, const double* mask = nullptr);
 double clebsch(int tj1, int tm1, int tj2, int tm2, int tJ, int tM);
 
-// pn part by pair blocks (pntile.hip): tables built with the Hamiltonian; the product adds
-// the pn part of H V to W (FP64, W already holding the identical-particle parts)
+// pn part by pair blocks (pntile.hip): tables built with the Hamiltonian; the product adds the pn
+// part of H V to W (W already holding the identical-particle parts)
 void build_pn_tiles(Model& m);
-// (reduce false: the last 16-column tile stays in the slot buffer for the own-row kernel to sum)
+// 16-byte chunks of a slot row of `cols` columns: with valid columns, and as laid out
+int pn_slot_chunks(size_t elt, int cols);
+int pn_slot_stride(size_t elt, int cols);
+// (reduce false, one batch and one column tile: the slots stay for the own-row kernel to sum)
 template <class T>
 void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int64_t ldw, hipStream_t s, bool reduce);
+
+// One proton row of W that a batch of pair blocks contributes to: its neutron states are
+// consecutive rows from `row`; tent[e0 .. e0 + ne) name its slot rows.
+struct PNRow {
+  int64_t row;
+  int dn, e0, ne, pad;
+};
 
 // device launchers (hv.hip)
 void launch_apply(const Model& m, int precision, int nb, const void* V, int64_t ldv, void* W, int64_t ldw,

@@ -14,12 +14,16 @@
 // a = c is a proton number operator, and its core is the target minus a), so the pn part of W is
 //   W[t] += sum over the n_prot * n_neut core pairs of t of  s_t (H_M (s V))[t].
 // A wavefront takes one core pair: it lists the allowed pairs with a ballot, gathers the source
-// rows (16 columns, one 128-byte line each) with their signs, multiplies by the block of H_M on
-// the matrix cores (v_mfma_f64_16x16x4f64), and writes each target row into the slot named by
-// the positions of x in the target's proton word and of u in its neutron word. Every slot of
-// every basis state is written exactly once per product, so the second kernel sums the slots
-// into W in a fixed order: no atomics, and the result does not depend on scheduling.
+// rows (16 columns, or 32 in FP32: one 128-byte line each) with their signs, multiplies by the block
+// of H_M on the matrix cores, and writes each target row into a slot of its own.
+//
+// Slots. The proton cores are worked through in batches. A batch owns a slot row for every
+// (core K_p, x, position of u in the target's neutron word, target neutron state), so each slot is
+// written exactly once, and the target rows K_p + x then add their slots to W in a fixed order:
+// no atomics, and the result does not depend on scheduling. Two slot buffers alternate: one launch
+// computes a batch and adds the previous one to W.
 #include <algorithm>
+#include <array>
 #include <cstdlib>
 #include <map>
 
@@ -35,8 +39,11 @@ template <class T>
 struct PNTileArgs {
   const T* V;
   T* Z;
-  int c0, cval;  // column tile: first column, valid columns (<= 16)
-  int ns, nneut, D, vrow;  // vrow: bytes per row of V
+  // column tile: first column, valid columns, lanes of a row (a power of two), 16-byte chunks of a slot row
+  // (written, and holding valid columns)
+  int c0, cval, lr, cpr, cprv;
+  int ns;
+  int64_t vrow;  // bytes per row of V
   const int* rkp;  // [core * ns + state]: position << 24 | local index of core + state, -1 inside
   const int* rkn;
   const int* blk_off;  // block offsets (the tables are used only while D < 2^31)
@@ -46,206 +53,324 @@ struct PNTileArgs {
   const int* hb_off;
   const T* hb;
   const int* rect;    // per rectangle: pair block, first entry of its list in rblk
-  const int* rblk;    // per rectangle and pair: block of the target's sectors, -1 if none
+  const int* rblk;    // per rectangle and pair: target block << 1 | parity of its neutron sector, -1 if none
+  const int* zoff;    // [(core * ns + x) * 2 + neutron parity]: first slot row in the batch
+  int zstep;          // slot rows between positions of u (0: the neutron states of the target's sector)
   const int4* items;  // per work item: rectangle, proton core, first neutron core, count
-  int nitems;
+  int nitems, spread;  // spread: taken in order by all XCDs, else a contiguous range for each
+  unsigned vbytes, zbytes;  // of V (where it stays below 4 GiB) and of a slot buffer
+  // the previous batch, added to W by the first nred workgroups
+  const T* Zr;
+  T* W;
+  int64_t ldw;
+  const PNRow* rows;
+  const int* tent;
+  int nred, nchunk, nrows, nneut, wvec;
 };
 
-// The product of one core pair: Z rows of its d allowed targets = (staged block) x (signed source
-// rows), DTM row tiles of 16 targets at most (d <= 16 DTM); sources k = 4 ks + l / 16 in groups
-// of 8 steps whose loads are issued together.
-template <class T, int DTM>
-__device__ __forceinline__ void tile_mfma(const T* Hs, const unsigned* Rv, const int* Pi, int h, int KS, int DT,
-                                          const int (&tb)[DTM], int kq, const T (&bop)[8],
-                                          typename Mfma<T>::acc (&acc)[DTM]) {
+constexpr int RED_ROWS = 64;  // target rows of one reducing workgroup
+
+// W[row + t][c0 + c] += the slots of target row t, entry by entry and position by position
+template <class T>
+__device__ __forceinline__ void add_slots(const PNTileArgs<T>& a, int bid) {
+  constexpr int VPC = 16 / (int)sizeof(T);  // values per 16 bytes
+  typedef T zv __attribute__((ext_vector_type(VPC)));
+  const int ri = bid / a.nchunk, t0 = (bid % a.nchunk) * RED_ROWS;
+  if (ri >= a.nrows) return;
+  const PNRow r = a.rows[ri];
+  const int n = min(RED_ROWS, r.dn - t0) * a.cprv;  // not positive: a chunk beyond this row
+  const int64_t step = (int64_t)(a.zstep ? a.zstep : r.dn) * a.cpr;
+  for (int e = threadIdx.x; e < n; e += 256) {
+    const int t = t0 + e / a.cprv, k = e % a.cprv;
+    T* w = a.W + (r.row + t) * a.ldw + a.c0 + VPC * k;
+    const bool full = a.wvec && VPC * k + VPC <= a.cval;
+    zv v;
+    if (full) {
+      v = *reinterpret_cast<const zv*>(w);
+    } else {
 #pragma unroll
-  for (int j = 0; j < 8; j++) {
-    if (8 * h + j < KS) {
-      const int kk = 4 * (8 * h + j) + kq;
-      const T b = flip_if(bop[j], Rv[kk] & 1u);
-      const int pk = Pi[kk];
-      T av[DTM];
-#pragma unroll
-      for (int mt = 0; mt < DTM; mt++) av[mt] = Hs[tb[mt] + pk];
-#pragma unroll
-      for (int mt = 0; mt < DTM; mt++)
-        if (mt < DT) acc[mt] = Mfma<T>::run(av[mt], b, acc[mt]);
+      for (int j = 0; j < VPC; j++) v[j] = VPC * k + j < a.cval ? w[j] : T(0);
     }
-  }
-}
-
-template <class T, int DTM>
-__device__ __forceinline__ void tile_init(const int* Pi, int HW, int c, int (&tb)[DTM],
-                                          typename Mfma<T>::acc (&acc)[DTM]) {
+    for (int i = 0; i < r.ne; i++) {
+      const zv* z = reinterpret_cast<const zv*>(a.Zr) + ((int64_t)a.tent[r.e0 + i] + t) * a.cpr + k;
+      int q = 0;
+      for (; q + 4 <= a.nneut; q += 4) {  // four in flight
+        zv zq[4];
 #pragma unroll
-  for (int mt = 0; mt < DTM; mt++) {
-    tb[mt] = Pi[16 * mt + c] * HW;
-    acc[mt] = typename Mfma<T>::acc{0, 0, 0, 0};
-  }
-}
-
-template <class T, int DTM>
-__device__ __forceinline__ void tile_store(const unsigned* Rz, int d, int DT, int c, int kq, bool cok, char* Zb,
-                                           const typename Mfma<T>::acc (&acc)[DTM]) {
+        for (int j = 0; j < 4; j++) zq[j] = __builtin_nontemporal_load(z + (q + j) * step);
 #pragma unroll
-  for (int mt = 0; mt < DTM; mt++) {
-    if (mt < DT) {
-#pragma unroll
-      for (int v = 0; v < 4; v++) {
-        const int i = 16 * mt + Mfma<T>::row(kq, v);
-        const unsigned z = Rz[i];
-        if (i < d && cok)
-          __builtin_nontemporal_store(flip_if((T)acc[mt][v], z & 1u),
-                                      reinterpret_cast<T*>(Zb + ((z & ~63u) + (unsigned)c * (unsigned)sizeof(T))));
+        for (int j = 0; j < 4; j++) v += zq[j];
       }
+      for (; q < a.nneut; q++) v += __builtin_nontemporal_load(z + q * step);
     }
-  }
-}
-
-template <class T, int DTM>
-__device__ __forceinline__ void tile_product(const T* Hs, const unsigned* Rv, const unsigned* Rz, const int* Pi, int d,
-                                             int HW, int c, int kq, bool cok, unsigned cb, const char* Vb, char* Zb) {
-  const int KS = (d + 3) >> 2, DT = (d + 15) >> 4;
-  int tb[DTM];
-  typename Mfma<T>::acc acc[DTM];
-  tile_init<T, DTM>(Pi, HW, c, tb, acc);
+    if (full) {
+      *reinterpret_cast<zv*>(w) = v;
+    } else {
 #pragma unroll
-  for (int h = 0; h < DTM / 2; h++) {
-    T bop[8];
-    tile_loads<T>(Rv, h, kq, cb, Vb, bop);
-    tile_mfma<T, DTM>(Hs, Rv, Pi, h, KS, DT, tb, kq, bop, acc);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  tile_store<T, DTM>(Rz, d, DT, c, kq, cok, Zb, acc);
-}
-
-// Two core pairs of at most 32 allowed pairs each: the loads of both are issued before the
-// products, so a wavefront keeps twice the rows in flight.
-template <class T>
-__device__ __forceinline__ void tile_product2(const T* Hs, const unsigned* RvA, const unsigned* RzA, const int* PiA,
-                                              int dA, const unsigned* RvB, const unsigned* RzB, const int* PiB, int dB,
-                                              int HW, int c, int kq, bool cok, unsigned cb, const char* Vb, char* Zb) {
-  const int KSA = (dA + 3) >> 2, DTA = (dA + 15) >> 4, KSB = (dB + 3) >> 2, DTB = (dB + 15) >> 4;
-  T bA[8], bB[8];
-  tile_loads<T>(RvA, 0, kq, cb, Vb, bA);
-  tile_loads<T>(RvB, 0, kq, cb, Vb, bB);
-  int tbA[2], tbB[2];
-  typename Mfma<T>::acc aA[2], aB[2];
-  tile_init<T, 2>(PiA, HW, c, tbA, aA);
-  tile_init<T, 2>(PiB, HW, c, tbB, aB);
-  tile_mfma<T, 2>(Hs, RvA, PiA, 0, KSA, DTA, tbA, kq, bA, aA);
-  tile_store<T, 2>(RzA, dA, DTA, c, kq, cok, Zb, aA);
-  tile_mfma<T, 2>(Hs, RvB, PiB, 0, KSB, DTB, tbB, kq, bB, aB);
-  tile_store<T, 2>(RzB, dB, DTB, c, kq, cok, Zb, aB);
-}
-
-// One work item: a proton core K_p and up to PN_TPB neutron cores of one (2M, parity) group; the
-// four wavefronts take every fourth core pair. Per core pair the allowed pairs are listed in LDS
-// (V byte offset | source sign, slot byte offset | target sign, pair index); the list is padded
-// to 64 entries with a valid row and the pair index D2, whose row and column of the staged block
-// are zero, so the products need no masks.
-template <class T>
-__global__ __launch_bounds__(256, 4) void pn_tile_kernel(PNTileArgs<T> a) {
-  extern __shared__ __align__(16) char hs_[];  // (widest block + 1)^2 values
-  T* Hs = reinterpret_cast<T*>(hs_);
-  __shared__ int Po[PN_MAXPAIR];  // per pair: offset of its block (-1: no block)
-  __shared__ int Pd[PN_MAXPAIR];  // per pair: neutron sector size of its block
-  __shared__ int Ps[PN_MAXPAIR];  // per pair: x | u << 8
-  __shared__ unsigned Rv[4][2][64];
-  __shared__ unsigned Rz[4][2][64];
-  __shared__ int Pi[4][2][64];
-  const int item = pn_xcd_item(blockIdx.x, a.nitems);
-  if (item >= a.nitems) return;
-  const int4 it = a.items[item];
-  const int k = a.rect[2 * it.x], rb0 = a.rect[2 * it.x + 1];
-  const int q0 = a.pr_off[k], D2 = a.pr_off[k + 1] - q0, HW = D2 + 1;
-  const T* hg = a.hb + a.hb_off[k];
-  for (int i = threadIdx.x / 64; i < HW; i += 4)
-    for (int j = threadIdx.x % 64; j < HW; j += 64) Hs[i * HW + j] = (i < D2 && j < D2) ? hg[i * D2 + j] : T(0);
-  for (int e = threadIdx.x; e < D2; e += 256) {
-    Ps[e] = a.pr_xu[q0 + e];
-    const int b = a.rblk[rb0 + e];
-    Po[e] = b >= 0 ? a.blk_off[b] : -1;
-    Pd[e] = b >= 0 ? a.blk_dn[b] : 0;
-  }
-  __syncthreads();
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int c = l & 15, kq = l >> 4;
-  const bool cok = c < a.cval;
-  // column byte; beyond the tile: a valid column
-  const unsigned cb = (unsigned)(a.c0 + min(c, a.cval - 1)) * (unsigned)sizeof(T);
-  const int lp = min(l, D2 - 1);
-  const int xu = Ps[lp], us = xu >> 8;
-  const int poff = Po[lp], pdn = Pd[lp];
-  const int rp = a.rkp[it.y * a.ns + (xu & 255)];  // the proton core is fixed for the item
-  const bool lok = l < D2 && poff >= 0 && rp >= 0;
-  const int bp = rp >> 24;
-  const int rowp = poff + (rp & 0xFFFFFF) * pdn;
-  const char* Vb = reinterpret_cast<const char*>(a.V);
-  char* Zb = reinterpret_cast<char*>(a.Z);
-  // the list of one core pair (neutron core entry rn) into buffer q; returns its allowed pairs
-  auto list = [&](int rn, int q) __attribute__((always_inline)) {
-    const bool ok = lok && rn >= 0;
-    const uint64_t mask = __ballot(ok);
-    const int d = __popcll(mask);
-    if (d == 0) return 0;  // uniform
-    const int below = __popcll(mask & ((1ull << l) - 1));
-    const int bn = rn >> 24;
-    const int row = rowp + (rn & 0xFFFFFF);
-    const unsigned sg = (unsigned)((bp + bn) & 1);
-    const int lead = __builtin_amdgcn_readlane(row, __builtin_ctzll(mask));
-    if (ok) {
-      Rv[w][q][below] = (unsigned)row * (unsigned)a.vrow | sg;
-      Rz[w][q][below] = ((unsigned)((bp * a.nneut + bn) * a.D + row) << Mfma<T>::ZSHIFT) | sg;
-      Pi[w][q][below] = l;
-    } else {  // padding: a valid row, the zero pair
-      const int pad = d + l - below;
-      Rv[w][q][pad] = (unsigned)lead * (unsigned)a.vrow;
-      Pi[w][q][pad] = D2;
+      for (int j = 0; j < VPC; j++)
+        if (VPC * k + j < a.cval) w[j] = v[j];
     }
-    return d;
-  };
-  int cn = it.z + w;
-  const int cend = it.z + it.w;
-  // neutron-core entries of the next two core pairs of this wavefront, loaded one step ahead
-  int rnA = cn < cend ? a.rkn[cn * a.ns + us] : -1;
-  int rnB = cn + 4 < cend ? a.rkn[(cn + 4) * a.ns + us] : -1;
-  for (; cn < cend; cn += 8) {
-    const int rA = rnA, rB = rnB;
-    const bool hasB = cn + 4 < cend;
-    if (cn + 8 < cend) rnA = a.rkn[(cn + 8) * a.ns + us];
-    if (cn + 12 < cend) rnB = a.rkn[(cn + 12) * a.ns + us];
-    const int dA = list(rA, 0);
-    const int dB = hasB ? list(rB, 1) : 0;
+  }
+}
+
+// Per-item tables in LDS: the pair states that the proton core allows, in order (neutron state u,
+// first V row of proton row K_p + x, first slot row of the core and x, position of x in the
+// target's proton word, slot rows between positions of u, index in the pair block).
+struct PairList {
+  int u[PN_MAXPAIR], row[PN_MAXPAIR], z[PN_MAXPAIR], pos[PN_MAXPAIR], step[PN_MAXPAIR], id[PN_MAXPAIR];
+};
+
+// A byte offset beyond every V and slot offset: buffer loads return 0 there, stores write nothing.
+constexpr unsigned NO_ROW = 0xFFFF0000u;
+
+// Buffer accesses. Slot rows of 64 bytes or more are streamed past the caches (NT): they are read back by
+// a later kernel; narrower rows are left for the L2 to merge into whole lines.
+#if defined(__HIP_DEVICE_COMPILE__)  // buffer descriptors exist only in the device pass
+template <int BYTES>
+struct Buf;
+template <>
+struct Buf<4> {
+  typedef unsigned raw;
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
+  }
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+template <>
+struct Buf<8> {
+  typedef unsigned raw __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
+  }
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+template <>
+struct Buf<16> {
+  typedef unsigned raw __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
+  }
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+
+// The core pairs of one item whose proton core allows d <= 4 KS pair states. The block is the same for
+// every neutron core, so the 16 columns of a matrix instruction are shared by KN of them: lane c
+// serves neutron core c / lr and VPL adjacent columns (one load or store of up to 16 bytes), and VPL
+// instructions take a lane's columns one after the other. A wavefront lists KN neutron cores at a
+// time, a lane per pair state (V offset and slot offset, halved, with the sign on top; NO_ROW where the
+// neutron core holds u), runs the KS k-steps of each 16-target tile over the block's fragments, and
+// during the last tile gathers each k-step's source rows of the next KN cores into the registers that
+// the step has just used.
+template <class T, int VPL, int KN, bool BIG, int KS>
+struct CorePairs {
+  static constexpr int LP = KS <= 4 ? 16 : KS <= 8 ? 32 : 64, PPO = 64 / LP;
+  static constexpr int NO = KN > PPO ? KN / PPO : 1, DT = (KS + 3) / 4;
+  static constexpr int LW = NO * 64;  // words of one list
+  typedef typename Cols<T, VPL>::type cols;
+  typedef Buf<(int)sizeof(cols)> B;
+  const PNTileArgs<T>& a;
+  const T* Af;
+  unsigned* L;  // this wavefront's lists: [stage][V offsets, slot offsets][LW]
+  int first, count;
+  int l, c, kq, q, pu;
+  bool have;
+  unsigned vrow, vh, rh, prow, pz, pstep, psg, cb, sb, at0;
+  __amdgpu_buffer_rsrc_t vs, zs;
+  int en[NO];
+
+  __device__ __forceinline__ CorePairs(const PNTileArgs<T>& a_, const PairList& P, int d, const T* Af_, unsigned* L_,
+                                       int first_, int count_)
+      : a(a_), Af(Af_), L(L_), first(first_), count(count_) {
+    l = threadIdx.x & 63;
+    c = l & 15;
+    kq = l >> 4;
+    const int i = min(l % LP, d - 1);
+    have = l % LP < d;
+    vrow = (unsigned)a.vrow;
+    vh = vrow >> 1;
+    rh = (unsigned)(a.lr * VPL * (int)sizeof(T)) >> 1;
+    pu = P.u[i];
+    prow = BIG ? (unsigned)P.row[i] : (unsigned)P.row[i] * vh;
+    pz = (unsigned)P.z[i] * rh;
+    pstep = (unsigned)P.step[i] * rh;
+    psg = (unsigned)P.pos[i];
+    q = min(c / a.lr, KN - 1);  // lanes beyond KN * lr repeat the last core
+    // columns of this lane: the last one of a ragged row overlaps its neighbour (the same values at the same
+    // place), and lanes beyond it repeat those columns and fill the slot row up
+    const int c1 = VPL * (c % a.lr), c2 = min(c1, a.cval - VPL);
+    cb = (unsigned)c2 * (unsigned)sizeof(T);
+    sb = (unsigned)(c1 < a.cval ? c2 : c1) * (unsigned)sizeof(T);
+    at0 = (unsigned)(q * LP + kq);
+    vs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.V + a.c0), (short)0, (int)a.vbytes, 0x00020000);
+    zs = __builtin_amdgcn_make_buffer_rsrc((void*)a.Z, (short)0, (int)a.zbytes, 0x00020000);
+  }
+  // neutron-core table entries of the KN cores from n on
+  __device__ __forceinline__ void entries(int n) {
+#pragma unroll
+    for (int o = 0; o < NO; o++) {
+      const int core = n + o * PPO + l / LP;
+      en[o] = core < count && o * PPO + l / LP < KN ? a.rkn[(first + core) * a.ns + pu] : -1;
+    }
+  }
+  // lists the KN cores whose entries are held, then fetches the entries from `next` on
+  __device__ __forceinline__ void list(int buf, int next) {
+    unsigned* const Rv = L + buf * 2 * LW;
+#pragma unroll
+    for (int o = 0; o < NO; o++) {
+      const int rn = en[o];
+      const bool ok = have && rn >= 0;
+      const unsigned loc = (unsigned)rn & 0xFFFFFFu, pos = (unsigned)rn >> 24;
+      const unsigned sg = (psg + pos) << 31;
+      Rv[o * 64 + l] = ok ? (BIG ? prow + loc : prow + __umul24(loc, vh)) | sg : BIG ? ~0u : NO_ROW >> 1;
+      Rv[LW + o * 64 + l] = ok ? (pz + pos * pstep + __umul24(loc, rh)) | sg : NO_ROW >> 1;
+    }
+    entries(next);
     // the lists are written and read by this wavefront only: LDS operations of one wavefront
     // complete in order, so only the compiler must keep them in place
     __builtin_amdgcn_wave_barrier();
-    if (dA > 0 && dA <= 32 && dB > 0 && dB <= 32) {
-      tile_product2<T>(Hs, Rv[w][0], Rz[w][0], Pi[w][0], dA, Rv[w][1], Rz[w][1], Pi[w][1], dB, HW, c, kq, cok, cb, Vb,
-                       Zb);
+  }
+  __device__ __forceinline__ cols gather(const unsigned* Rv, int j) {
+    const unsigned o = Rv[at0 + 4 * j];
+    if constexpr (BIG) {
+      const bool no = o == ~0u;
+      const char* p = reinterpret_cast<const char*>(a.V + a.c0) + ((uint64_t)(no ? 0u : o & 0x7FFFFFFFu) * vrow + cb);
+      cols x;
+      __builtin_memcpy(&x, p, sizeof(x));
+      return no ? cols(0) : x;
     } else {
-      if (dA > 32) tile_product<T, 4>(Hs, Rv[w][0], Rz[w][0], Pi[w][0], dA, HW, c, kq, cok, cb, Vb, Zb);
-      else if (dA > 0) tile_product<T, 2>(Hs, Rv[w][0], Rz[w][0], Pi[w][0], dA, HW, c, kq, cok, cb, Vb, Zb);
-      if (dB > 32) tile_product<T, 4>(Hs, Rv[w][1], Rz[w][1], Pi[w][1], dB, HW, c, kq, cok, cb, Vb, Zb);
-      else if (dB > 0) tile_product<T, 2>(Hs, Rv[w][1], Rz[w][1], Pi[w][1], dB, HW, c, kq, cok, cb, Vb, Zb);
+      return __builtin_bit_cast(cols, B::load(vs, (o << 1) + cb));
     }
-    __builtin_amdgcn_wave_barrier();
   }
-}
+  static __device__ __forceinline__ T value(const cols& x, int t) {
+    if constexpr (VPL == 1) return x;
+    else return x[t];
+  }
+  static __device__ __forceinline__ cols flipped(cols x, unsigned o) {
+    if constexpr (VPL == 1) {
+      return flip_if(x, o >> 31);
+    } else {
+#pragma unroll
+      for (int t = 0; t < VPL; t++) x[t] = flip_if((T)x[t], o >> 31);
+      return x;
+    }
+  }
+  __device__ __forceinline__ void run() {
+    int n = (int)(threadIdx.x >> 6) * KN;
+    if (n >= count) return;
+    cols b[KS];
+    entries(n);
+    list(0, n + 4 * KN);
+#pragma unroll
+    for (int j = 0; j < KS; j++) b[j] = gather(L, j);
+    int buf = 0;
+    for (; n < count; n += 4 * KN) {
+      const unsigned* const Rv = L + buf * 2 * LW;
+      buf ^= 1;
+      list(buf, n + 8 * KN);  // beyond the last core: no rows
+      const unsigned* const Nv = L + buf * 2 * LW;
+#pragma unroll
+      for (int mt = 0; mt < DT; mt++) {
+        typename Mfma<T>::acc acc[VPL];
+#pragma unroll
+        for (int t = 0; t < VPL; t++) acc[t] = typename Mfma<T>::acc{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < KS; j++) {
+          if (mt == 0) b[j] = flipped(b[j], Rv[at0 + 4 * j]);
+          const T av = Af[(mt * KS + j) * 64 + l];
+#pragma unroll
+          for (int t = 0; t < VPL; t++) acc[t] = Mfma<T>::run(av, value(b[j], t), acc[t]);
+          if (mt == DT - 1) b[j] = gather(Nv, j);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          const unsigned z = Rv[LW + q * LP + 16 * mt + Mfma<T>::row(kq, v)];
+          cols x;
+          if constexpr (VPL == 1) {
+            x = (T)acc[0][v];
+          } else {
+#pragma unroll
+            for (int t = 0; t < VPL; t++) x[t] = (T)acc[t][v];
+          }
+          B::template store<(VPL > 1 && KN <= 4)>(__builtin_bit_cast(typename B::raw, flipped(x, z)), zs, (z << 1) + sb);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+};
+#endif
 
-// W[t][c0 + c] += sum of the S slots of t, in slot order
-template <class T>
-__global__ void pn_reduce_kernel(const T* __restrict__ Z, int S, int64_t D, T* __restrict__ W, int64_t ldw, int c0,
-                                 int cval) {
-  const int64_t n = D * 16;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e & 15);
-    if (c >= cval) continue;
-    const int64_t t = e >> 4;
-    T s = T(0);
-    for (int k = 0; k < S; k++) s += __builtin_nontemporal_load(Z + ((int64_t)k * D + t) * 16 + c);
-    W[t * ldw + c0 + c] += s;
+// One work item: a proton core K_p and a run of neutron cores of one (2M, parity) group. The pair
+// states that K_p leaves free are listed once, and the block of H_M over them is laid out as the
+// matrix instructions read it (one conflict-free LDS read per fragment). The neutron cores then
+// only mask sources and targets: their blocked pairs read zeros and write nothing. The first
+// workgroups of a launch add the previous batch.
+template <class T, int VPL, int KN, bool BIG>
+__global__ __launch_bounds__(256, 4) void pn_tile_kernel(PNTileArgs<T> a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __align__(16) char hs_[];  // fragments of the widest block
+  T* Af = reinterpret_cast<T*>(hs_);
+  __shared__ PairList P;
+  constexpr int LW = 4 * KN * 64;  // words of one wavefront's lists
+  __shared__ unsigned L[4 * LW];
+  if ((int)blockIdx.x < a.nred) {
+    add_slots<T>(a, blockIdx.x);
+    return;
   }
+  const int item = a.spread ? blockIdx.x - a.nred : pn_xcd_item(blockIdx.x - a.nred, a.nitems);
+  if (item >= a.nitems) return;
+  const int4 it = a.items[item];
+  const int k = a.rect[2 * it.x], rb0 = a.rect[2 * it.x + 1];
+  const int q0 = a.pr_off[k], D2 = a.pr_off[k + 1] - q0;
+  const T* hg = a.hb + a.hb_off[k];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int xu = a.pr_xu[q0 + min(l, D2 - 1)], x = xu & 255;
+  const int tb = a.rblk[rb0 + min(l, D2 - 1)];
+  const int rp = a.rkp[it.y * a.ns + x];
+  const bool lok = l < D2 && tb >= 0 && rp >= 0;
+  const uint64_t mask = __ballot(lok);
+  const int d = __popcll(mask);
+  if (d == 0) return;  // the same for every wavefront
+  if (w == 0 && lok) {
+    const int i = __popcll(mask & ((1ull << l) - 1));
+    const int dn = a.blk_dn[tb >> 1];
+    P.u[i] = xu >> 8;
+    P.row[i] = a.blk_off[tb >> 1] + (rp & 0xFFFFFF) * dn;
+    P.z[i] = a.zoff[(it.y * a.ns + x) * 2 + (tb & 1)];
+    P.pos[i] = rp >> 24;
+    P.step[i] = a.zstep ? a.zstep : dn;
+    P.id[i] = l;
+  }
+  __syncthreads();
+  const int KS = (d + 7) / 8 * 2, nf = (KS + 3) / 4 * KS;
+  for (int f = w; f < nf; f += 4) {
+    const int i = f / KS * 16 + (l & 15), j = f % KS * 4 + (l >> 4);
+    Af[f * 64 + l] = i < d && j < d ? hg[P.id[i] * D2 + P.id[j]] : T(0);
+  }
+  __syncthreads();
+#define TRBL_PAIRS(K) \
+  case K: CorePairs<T, VPL, KN, BIG, K>(a, P, d, Af, L + w * LW, it.z, it.w).run(); break
+  switch (KS) {
+    TRBL_PAIRS(2);
+    TRBL_PAIRS(4);
+    TRBL_PAIRS(6);
+    TRBL_PAIRS(8);
+    TRBL_PAIRS(10);
+    TRBL_PAIRS(12);
+    TRBL_PAIRS(14);
+    TRBL_PAIRS(16);
+  }
+#undef TRBL_PAIRS
+#endif
 }
 
 }  // namespace
@@ -254,6 +379,7 @@ void build_pn_tiles(Model& m) {
   PNTiles& T = m.pn;
   T.on = false;
   T.z.release();
+  T.batches.clear();
   const char* env = std::getenv("TRBL_PN_TILES");
   if (env && env[0] == '0') return;
   T.force = env && env[0] == '2';
@@ -272,13 +398,17 @@ void build_pn_tiles(Model& m) {
   int maxp = 0;
   for (auto& v : pairs) maxp = std::max(maxp, (int)v.size());
   if (maxp > PN_MAXPAIR) return;
-  // Every slot row (16 values written, then read back) carries the products of one core pair:
-  // on average about L = (pair-weighted mean block size) x (share of the proton states outside a
-  // proton core) x (the same for neutrons) source pairs. With few of them the slot traffic costs
-  // more than the elements it carries: pf 3+3, 4+4 and 5+3 (L = 31 to 35) run 1.0 to 2.3 times
-  // faster on the pair blocks (FP64 at 8 and 16 columns, FP32 at 16), sd 5+5 and 6+6 (L = 9.0
-  // and 6.9) up to 2.9 times slower, sd 4+4 (L = 11.4) slower at 8 columns and faster at 16. The
-  // pair blocks are taken from L = 16 on (TRBL_PN_TILES=2 takes them regardless).
+  // Where the pair blocks are built (ms per product, jump lists / pair blocks; TRBL_PN_TILES=2 builds them
+  // regardless). A slot row, written and read back, carries the products of one core pair: on average
+  // about L = (pair-weighted mean block size) x (share of the proton states outside a proton core) x (the
+  // same for neutrons) source pairs. From L = 11 on (all pf spaces, sd up to 4+4; FP64 at 1, 8, 16 columns):
+  // pf 4+4 (L = 31) 1.85 / 0.93, 3.10 / 1.70, 5.49 / 3.24; pf 3+3 0.189 / 0.085, 0.276 / 0.122, 0.355 /
+  // 0.177; sd 4+4 (11.4) 0.065 / 0.057, 0.080 / 0.062, 0.113 / 0.086; sd 4+5 (10.1) 0.087 / 0.061, 0.089 /
+  // 0.085, 0.131 / 0.134; sd 6+6 (6.9) 0.087 / 0.111, 0.130 / 0.186, 0.180 / 0.285. Below L = 16 products
+  // of more than one column tile keep the jump lists (sd 4+4, FP64, 32 columns: 0.130 / 0.171).
+  // Below 2,500 states the launches decide (sd 2+2, D = 640, 4 columns: 0.041 / 0.052; pf 3+1, D = 2,550:
+  // 0.074 / 0.058), and with one proton the jump lists stage each source row for few targets
+  // (pf 1+4, 8 columns: 0.092 / 0.107; pf 4+1: 0.322 / 0.063).
   {
     double n1 = 0.0, n2 = 0.0;
     for (auto& v : pairs) {
@@ -286,7 +416,8 @@ void build_pn_tiles(Model& m) {
       n2 += (double)v.size() * (double)v.size();
     }
     const double L = n2 / n1 * (double)(ns - (m.n_prot - 1)) / ns * (double)(ns - (m.n_neut - 1)) / ns;
-    if (L < 16.0 && !T.force) return;
+    if ((L < 11.0 || m.dim < 2500 || m.n_prot == 1) && !T.force) return;
+    T.one_tile = L < 16.0 && !T.force;
   }
   std::vector<int> pr_off(nk + 1, 0), pr_xu, hb_off(nk + 1, 0);
   for (int k = 0; k < nk; k++) {
@@ -382,7 +513,7 @@ void build_pn_tiles(Model& m) {
         auto ip = secid[0].find({gp.tm + m.st_tm[x], gp.par * stpar(x)});
         auto in = secid[1].find({gn.tm + m.st_tm[u], gn.par * stpar(u)});
         const int b = (ip != secid[0].end() && in != secid[1].end()) ? bos[ip->second * nnsec + in->second] : -1;
-        pb.push_back(b);
+        pb.push_back(b >= 0 ? b << 1 | (m.sp[1].sectors[in->second].par < 0 ? 1 : 0) : -1);
         any = any || b >= 0;
       }
       if (!any) continue;
@@ -391,50 +522,135 @@ void build_pn_tiles(Model& m) {
       rblk.insert(rblk.end(), pb.begin(), pb.end());
     }
   if (rect.empty()) return;
-  // work items: per proton core, per neutron group with a rectangle, up to `chunk` neutron cores
-  // (TRBL_PN_CHUNK: a tuning override). Items go to the XCDs in contiguous ranges, and the
-  // cores of a group in runs of 16 consecutive (colex) cores: one neutron group after the other
-  // for the 16 cores of a run, so that the items in flight on an XCD share more source rows
-  // in its L2 (pf 4+4: FP64 H.V 3.39 against 3.46 ms with one core at a time; runs of 8, 12,
-  // 20, 32, 64 and 128 gave 3.40 to 3.45 ms).
-  int chunk = PN_TPB;
-  if (const char* ev = std::getenv("TRBL_PN_CHUNK")) chunk = std::max(8, std::min(PN_TPB, std::atoi(ev)));
-  constexpr int CORE_RUN = 16;
-  std::vector<int> items;
-  const int ngn = (int)groups[1].size();
-  for (int ip = 0; ip < (int)groups[0].size(); ip++) {
-    const int c_lo = groups[0][ip].start, c_hi = c_lo + groups[0][ip].count;
-    for (int t0 = c_lo; t0 < c_hi; t0 += CORE_RUN)
-      for (int in = 0; in < ngn; in++) {
-        const int r = rect_of[ip * ngn + in];
-        if (r < 0) continue;
-        const Group& gn = groups[1][in];
-        for (int cp = t0; cp < std::min(c_hi, t0 + CORE_RUN); cp++)
-          for (int c0 = 0; c0 < gn.count; c0 += chunk)
-            items.insert(items.end(), {r, cp, gn.start + c0, std::min(chunk, gn.count - c0)});
+  // V rows and slot rows are counted in 31 and 32 bits
+  if ((double)m.dim >= 2147483648.0) return;
+  // Slot rows of every proton core: for each x outside it and each neutron sector that completes
+  // K_p + x to a block of the space, n_neut rows per neutron state.
+  const int nc0 = (int)cw[0].size();
+  std::vector<int64_t> crow(nc0, 0);
+  std::vector<int> zoff((size_t)nc0 * ns * 2, -1);  // here: the target block
+  for (const Group& gp : groups[0])
+    for (int cp = gp.start; cp < gp.start + gp.count; cp++)
+      for (int x = 0; x < ns; x++) {
+        if (rk[0][(size_t)cp * ns + x] < 0) continue;
+        const auto ip = secid[0].find({gp.tm + m.st_tm[x], gp.par * stpar(x)});
+        if (ip == secid[0].end()) continue;
+        for (int q = 0; q < nnsec; q++) {
+          const int b = bos[ip->second * nnsec + q];
+          if (b < 0) continue;
+          zoff[((size_t)cp * ns + x) * 2 + (m.sp[1].sectors[q].par < 0 ? 1 : 0)] = b;
+          crow[cp] += (int64_t)m.n_neut * m.blocks[b].dn;
+        }
       }
-  }
-  TRBL_REQUIRE(items.size() / 4 < ((size_t)1 << 31) / 256, TRBL_E_INVALID, "too many core pairs for one launch");
-  // the slot buffer: S slots of 16 FP64 columns per basis state, sized within a quarter of the
-  // free device memory (larger spaces keep the jump-list kernel)
-  const int S = m.n_prot * m.n_neut;
-  const size_t zbytes = (size_t)S * (size_t)m.dim * 16 * sizeof(double);
-  // 32-bit byte offsets in the kernel: the slot buffer and V (rows of at most 64 columns) must
-  // stay below 4 GiB
-  if ((double)zbytes >= 4294967296.0 || (double)m.dim * 64 * 8 >= 4294967296.0) return;
+  // Batches: a single one while the slots of all cores stay below 4 GiB (128-byte rows) and a quarter of
+  // the free memory, else runs of proton cores of at most 4 Mi rows, two buffers of 512 MiB (pf 6+6,
+  // FP32 at 32 columns: 645 ms; 1 Mi rows 756, 2 Mi 658, 8 Mi 646, 32 Mi 614 to 634 ms, at 8 GB).
+  // TRBL_PN_BATCH: the most slot rows of a batch (a testing and tuning override).
   size_t fr = 0, tot = 0;
   TRBL_HIP(hipMemGetInfo(&fr, &tot));
+  int64_t all = 0, cap = 1 << 22;
+  for (int64_t r : crow) all += r;
+  if (all * 128 <= (int64_t)std::min<size_t>(NO_ROW, fr / 4)) cap = all;
+  if (const char* ev = std::getenv("TRBL_PN_BATCH")) cap = std::max(1ll, std::atoll(ev));
+  for (int64_t r : crow) cap = std::max(cap, r);
+  if (cap * 128 > (int64_t)NO_ROW) return;  // slot byte offsets in 32 bits
+  std::vector<int> bat0(1, 0);
+  int64_t run = 0, most = 0;
+  for (int cp = 0; cp < nc0; cp++) {
+    if (run + crow[cp] > cap) {
+      bat0.push_back(cp);
+      run = 0;
+    }
+    run += crow[cp];
+    most = std::max(most, run);
+  }
+  bat0.push_back(nc0);
+  const int nbat = (int)bat0.size() - 1;
+  // one batch: the slots of all targets lie one position pair after the other, [x][u][target]
+  T.zstep = nbat == 1 ? (int)m.dim : 0;
+  // Work items of a batch: per run of proton cores of one group, per neutron group with a rectangle, up
+  // to `chunk` neutron cores at a time (TRBL_PN_CHUNK: a tuning override) for each core of the run. Items go
+  // to the XCDs in contiguous ranges. One batch: 256 neutron cores, and runs of 16 consecutive (colex)
+  // cores, so that the items in flight on an XCD share source rows in its L2. Several: 64 and one core
+  // after the other, so that a batch has enough items for the chip (pf 6+6: 645 against 696 ms).
+  int chunk = nbat == 1 ? PN_TPB : 64;
+  if (const char* ev = std::getenv("TRBL_PN_CHUNK")) chunk = std::max(8, std::min(PN_TPB, std::atoi(ev)));
+  const int core_run = nbat == 1 ? 16 : 1;
+  std::vector<int> group_of(nc0);
+  for (int g = 0; g < (int)groups[0].size(); g++)
+    for (int cp = groups[0][g].start; cp < groups[0][g].start + groups[0][g].count; cp++) group_of[cp] = g;
+  std::vector<int64_t> blk_row0(m.blocks.size() + 1, 0);
+  for (size_t b = 0; b < m.blocks.size(); b++) blk_row0[b + 1] = blk_row0[b] + m.blocks[b].dp;
+  TRBL_REQUIRE(blk_row0.back() < ((int64_t)1 << 31), TRBL_E_INVALID, "too many proton rows");
+  const int ngn = (int)groups[1].size();
+  std::vector<int> items, tent;
+  std::vector<PNRow> trow;
+  for (int ib = 0; ib < nbat; ib++) {
+    PNTiles::Batch B{};
+    B.item0 = (int)(items.size() / 4);
+    B.row0 = (int)trow.size();
+    for (int t0 = bat0[ib]; t0 < bat0[ib + 1];) {
+      const int g = group_of[t0];
+      const int t1 = std::min(std::min(bat0[ib + 1], groups[0][g].start + groups[0][g].count), t0 + core_run);
+      for (int in = 0; in < ngn; in++) {
+        const int r = rect_of[g * ngn + in];
+        if (r < 0) continue;
+        const Group& gn = groups[1][in];
+        for (int c0 = 0; c0 < gn.count; c0 += chunk)
+          for (int cp = t0; cp < t1; cp++)
+            items.insert(items.end(), {r, cp, gn.start + c0, std::min(chunk, gn.count - c0)});
+      }
+      t0 = t1;
+    }
+    if (nbat > 1) {  // the costliest items first: a batch is a few items per workgroup slot
+      std::vector<std::pair<int64_t, std::array<int, 4>>> by_cost;
+      for (size_t i = 4 * (size_t)B.item0; i < items.size(); i += 4) {
+        const int k = rect[2 * items[i]], rb0 = rect[2 * items[i] + 1];
+        int d = 0;
+        for (size_t e = 0; e < pairs[k].size(); e++)
+          d += rblk[rb0 + e] >= 0 && rk[0][(size_t)items[i + 1] * ns + (pairs[k][e] & 255)] >= 0;
+        const int ks = (d + 7) / 8 * 2;
+        by_cost.push_back({-(int64_t)items[i + 3] * (400 + 64 * ks * ((ks + 3) / 4)),
+                           {items[i], items[i + 1], items[i + 2], items[i + 3]}});
+      }
+      std::stable_sort(by_cost.begin(), by_cost.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
+      for (size_t i = 0; i < by_cost.size(); i++)
+        for (int q = 0; q < 4; q++) items[4 * ((size_t)B.item0 + i) + q] = by_cost[i].second[q];
+    }
+    // slot rows and target rows of the batch
+    std::map<int64_t, std::vector<int>> to;  // target row (block row0 + proton row) -> first slot rows
+    int64_t at = 0;
+    for (int cp = bat0[ib]; cp < bat0[ib + 1]; cp++)
+      for (int x = 0; x < ns; x++)
+        for (int q = 0; q < 2; q++) {
+          int& z = zoff[((size_t)cp * ns + x) * 2 + q];
+          if (z < 0) continue;
+          const int b = z;
+          const int r = rk[0][(size_t)cp * ns + x], pl = r & 0xFFFFFF, dn = m.blocks[b].dn;
+          z = (int)(T.zstep ? (int64_t)(r >> 24) * m.n_neut * m.dim + m.blocks[b].off + (int64_t)pl * dn : at);
+          to[blk_row0[b] + pl].push_back(z);
+          at += (int64_t)m.n_neut * dn;
+        }
+    size_t b = 0;
+    for (auto& kv : to) {
+      while (kv.first >= blk_row0[b + 1]) b++;
+      const int dn = m.blocks[b].dn;
+      trow.push_back({m.blocks[b].off + (kv.first - blk_row0[b]) * dn, dn, (int)tent.size(), (int)kv.second.size(), 0});
+      tent.insert(tent.end(), kv.second.begin(), kv.second.end());
+      B.maxdn = std::max(B.maxdn, dn);
+    }
+    B.nitems = (int)(items.size() / 4) - B.item0;
+    B.nrows = (int)trow.size() - B.row0;
+    TRBL_REQUIRE(B.nitems < (1 << 22) && B.nrows < (1 << 22) / ((B.maxdn + RED_ROWS - 1) / RED_ROWS), TRBL_E_INVALID,
+                 "too many core pairs for one launch");
+    if (B.nitems > 0) T.batches.push_back(B);
+  }
+  TRBL_REQUIRE(items.size() < ((size_t)1 << 31), TRBL_E_INVALID, "too many core pairs");
+  T.nbuf = T.batches.size() > 1 ? 2 : 1;
+  T.buf_rows = most;
+  const size_t zbytes = (size_t)T.nbuf * (size_t)most * 128;
   if (zbytes > fr / 4) return;
-  T.S = S;
-  T.nk = nk;
-  T.nrect = (int)(rect.size() / 2);
-  T.ncore[0] = (int)cw[0].size();
-  T.ncore[1] = (int)cw[1].size();
   T.max_pairs = maxp;
-  T.tpb = PN_TPB;
-  T.items = (int64_t)(items.size() / 4);
-  T.cw[0].upload(cw[0]);
-  T.cw[1].upload(cw[1]);
   T.rk[0].upload(rk[0]);
   T.rk[1].upload(rk[1]);
   T.pr_off.upload(pr_off);
@@ -445,7 +661,10 @@ void build_pn_tiles(Model& m) {
   T.hb32.upload(hb32);
   T.rect.upload(rect);
   T.rblk.upload(rblk);
-  T.item0.upload(items);
+  T.items.upload(items);
+  T.zoff.upload(zoff);
+  T.trow.upload(trow);
+  T.tent.upload(tent);
   std::vector<int> boff32(m.blocks.size());
   for (size_t b = 0; b < m.blocks.size(); b++) boff32[b] = (int)m.blocks[b].off;
   T.boff.upload(boff32);
@@ -456,16 +675,58 @@ void build_pn_tiles(Model& m) {
   T.on = true;
 }
 
+template <class T, int VPL, int KN>
+static void run_batches(const PNTiles& P, PNTileArgs<T>& a, bool big, bool reduce, hipStream_t s) {
+  const int ks = (P.max_pairs + 7) / 8 * 2;
+  const size_t shm = (size_t)((ks + 3) / 4 * ks) * 64 * sizeof(T);
+  const int4* items = P.items.as<int4>();
+  const PNRow* rows = P.trow.as<PNRow>();
+  const int64_t bytes = P.buf_rows * a.cpr * 16;
+  a.zbytes = (unsigned)bytes;
+  char* const z = P.z.as<char>();
+  const int n = (int)P.batches.size();
+  for (int i = 0; i < n + (reduce ? 1 : 0); i++) {
+    a.nred = a.nitems = 0;
+    if (i > 0) {
+      const PNTiles::Batch& R = P.batches[i - 1];
+      a.nchunk = (R.maxdn + RED_ROWS - 1) / RED_ROWS;
+      a.nrows = R.nrows;
+      a.nred = (int)(((int64_t)R.nrows * a.nchunk + 7) / 8 * 8);
+      a.rows = rows + R.row0;
+      a.Zr = reinterpret_cast<const T*>(z + (size_t)((i - 1) % P.nbuf) * bytes);
+    }
+    if (i < n) {
+      const PNTiles::Batch& B = P.batches[i];
+      a.items = items + B.item0;
+      a.nitems = B.nitems;
+      a.Z = reinterpret_cast<T*>(z + (size_t)(i % P.nbuf) * bytes);
+    }
+    const dim3 grid((unsigned)(a.nred + (a.nitems + 7) / 8 * 8));
+    if (big) hipLaunchKernelGGL((pn_tile_kernel<T, VPL, KN, true>), grid, dim3(256), i < n ? shm : 0, s, a);
+    else hipLaunchKernelGGL((pn_tile_kernel<T, VPL, KN, false>), grid, dim3(256), i < n ? shm : 0, s, a);
+  }
+}
+
+// 16-byte chunks of a slot row: those with valid columns, and as laid out (a power of two, so that whole
+// lines are written)
+int pn_slot_chunks(size_t elt, int cols) { return (cols * (int)elt + 15) / 16; }
+int pn_slot_stride(size_t elt, int cols) {
+  int p = 1;
+  while (p < pn_slot_chunks(elt, cols)) p <<= 1;
+  return p;
+}
+
 template <class T>
 void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int64_t ldw, hipStream_t s, bool reduce) {
+  constexpr int VPC = 16 / (int)sizeof(T), WIDE = 128 / (int)sizeof(T);  // values per lane, most columns at once
   const PNTiles& P = m.pn;
   PNTileArgs<T> a{};
   a.V = V;
-  a.Z = P.z.as<T>();
+  a.W = W;
+  a.ldw = ldw;
   a.ns = m.ns;
   a.nneut = m.n_neut;
-  a.D = (int)m.dim;
-  a.vrow = (int)(ldv * sizeof(T));
+  a.vrow = ldv * (int64_t)sizeof(T);
   a.rkp = P.rk[0].as<int>();
   a.rkn = P.rk[1].as<int>();
   a.blk_off = P.boff.as<int>();
@@ -476,19 +737,28 @@ void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int6
   a.hb = (sizeof(T) == 8 ? P.hb : P.hb32).as<T>();
   a.rect = P.rect.as<int>();
   a.rblk = P.rblk.as<int>();
-  a.items = P.item0.as<int4>();
-  a.nitems = (int)P.items;
-  const unsigned grid = (unsigned)((P.items + 7) / 8 * 8);
-  const size_t shm = (size_t)(P.max_pairs + 1) * (P.max_pairs + 1) * sizeof(T);
-  // a wider product reuses the slot buffer per 16 columns, each tile summed into W in turn; with
-  // reduce false (one tile) the own-row kernel sums it
-  for (int c0 = 0; c0 < nb; c0 += 16) {
+  a.zoff = P.zoff.as<int>();
+  a.zstep = P.zstep;
+  a.spread = P.batches.size() > 1;
+  a.tent = P.tent.as<int>();
+  const bool big = (double)m.dim * (double)a.vrow > (double)NO_ROW || a.vrow >= (1 << 25);
+  for (int c0 = 0; c0 < nb; c0 += WIDE) {
     a.c0 = c0;
-    a.cval = std::min(16, nb - c0);
-    hipLaunchKernelGGL(pn_tile_kernel<T>, dim3(grid), dim3(256), shm, s, a);
-    if (reduce || c0 + 16 < nb)
-      hipLaunchKernelGGL(pn_reduce_kernel<T>, dim3(elementwise_grid(m.dim * 16)), dim3(256), 0, s, (const T*)a.Z, P.S,
-                         m.dim, W, ldw, c0, a.cval);
+    a.cval = std::min(WIDE, nb - c0);
+    a.vbytes = big ? 0u : (unsigned)(m.dim * a.vrow - c0 * (int64_t)sizeof(T));
+    a.wvec = (uintptr_t)(W + c0) % 16 == 0 && (ldw * (int64_t)sizeof(T)) % 16 == 0;
+    // neutron cores that share the 16 columns of a matrix instruction
+    a.cprv = pn_slot_chunks(sizeof(T), a.cval);
+    a.cpr = pn_slot_stride(sizeof(T), a.cval);
+    if (a.cval < VPC) {
+      a.lr = VPC;  // one value a lane
+      run_batches<T, 1, 16 / VPC>(P, a, big, reduce, s);
+      continue;
+    }
+    a.lr = a.cpr;
+    if (a.lr <= 2) run_batches<T, VPC, 8>(P, a, big, reduce, s);
+    else if (a.lr <= 4) run_batches<T, VPC, 4>(P, a, big, reduce, s);
+    else run_batches<T, VPC, 2>(P, a, big, reduce, s);
   }
   TRBL_HIP(hipGetLastError());
 }

@@ -44,6 +44,17 @@ __device__ __forceinline__ double flip_if(double x, unsigned s) {
 }
 __device__ __forceinline__ float flip_if(float x, unsigned s) { return __int_as_float(__float_as_int(x) ^ (int)(s << 31)); }
 
+// CT adjacent columns of one lane: CT column tiles interleave their columns (lane c of a 16-lane
+// group holds columns CT c .. CT c + CT - 1), so a lane's share of a row is one load or store.
+template <class T, int CT>
+struct Cols {
+  typedef T type __attribute__((ext_vector_type(CT)));
+};
+template <class T>
+struct Cols<T, 1> {
+  typedef T type;
+};
+
 template <class T>
 __device__ __forceinline__ void tile_loads(const unsigned* Rv, int h, int kq, unsigned cb, const char* Vb,
                                            T (&bop)[8]) {
