@@ -110,19 +110,14 @@ struct DeviceTables {
   DevBuf pwords, nwords, ppart, npart, psec_start, psec_size, nsec_start, nsec_size, blk_of_sec;
   DevBuf psec_tm, psec_par, nsec_tm, nsec_par;
   // jumps
-  DevBuf pj_start, pj_idx, pj_meta, nj_start, nj_idx, nj_meta, nj_pack;  // nj_* class-major
+  DevBuf pj_start, pj_idx, pj_meta, nj_start, nj_idx, nj_meta;  // nj_* class-major
   DevBuf pg_start, pg_desc;  // per proton SD: jump groups (class, first, end, source row) as int4
   DevBuf pg_cend;            // per jump group: first group after the run of its class
   DevBuf nj32;               // neutron jumps, class-major, packed: sign << 31 | op << 16 | source
   DevBuf nlane;              // per neutron SD slot (sector start + lane): the SD's index in its sector
   DevBuf h_off, h_ncol, h64, h32;
-  DevBuf pp_ptr, pp_col, pp_v64, pp_v32, nn_ptr, nn_col, nn_v64, nn_v32;
   DevBuf pe_off, pe_w, pe_col, pe_v64, pe_v32, ne_off, ne_w, ne_col, ne_v64, ne_v32;  // sliced ELL
   DevBuf blk_pslice0, blk_nslice0;  // first ELL slice of each block's proton / neutron sector
-  // gradient bins: per identical-particle operator entry / pn op pair, which m-scheme term
-  DevBuf pp_term, nn_term;  // per CSR entry: list range into term lists
-  DevBuf pp_tptr, pp_tid, pp_tsgn, nn_tptr, nn_tid, nn_tsgn;
-  DevBuf h_term;            // per pn table entry: m-scheme pn term id (-1 if none)
   // one species only, generated on the fly (fly.hip): ranking tables and the two-body terms
   // grouped by creation pair
   DevBuf fly_base, fly_rank, fly_perm, fly_wint, fly_soff, fly_sstart, fly_pstart, fly_cd, fly_h64, fly_h32, fly_e64,
@@ -209,6 +204,11 @@ struct MTerm {  // m-scheme two-body term c+_a c+_b c_d c_c (species-local state
   double h;
 };
 
+struct GradTables;  // gradient tables (grad.hip)
+struct GradTablesDelete {
+  void operator()(GradTables* t) const;
+};
+
 struct Model {
   // space
   std::vector<trbl_orbit> orbits;
@@ -237,7 +237,6 @@ struct Model {
   int max_hs_class = 0;  // most coefficient-table entries of one proton SD's jump groups of one class
   int max_hncol = 0;     // widest row of the pn coefficient table
   int max_dn = 0, max_dp = 0;
-  std::vector<int> h_off_host, h_ncol_host;
   std::vector<int> src_blk_host;        // per (block, class): source block or -1
   std::vector<int> sec_slice0[2];       // per species sector: first sliced-ELL slice
   std::vector<int> nlane_pos;           // per neutron SD: its lane position in its sector
@@ -248,7 +247,8 @@ struct Model {
   int fly_half = 0;  // m-states in the low part of the two-level ranking
   mutable DevBuf fly_buf[2];  // V and W in the internal order (FP32, FP64)
   mutable FlyTiles flyt;      // its two-body part as dense pair blocks (when the slot buffer fits)
-  mutable PNTiles pn;         // pn part as dense pair blocks (when its slot buffer fits)
+  mutable PNTiles pn;         // pn part as dense pair blocks
+  mutable std::unique_ptr<GradTables, GradTablesDelete> grad_tables;  // built by the first gradient
 };
 
 // host helpers (model.cpp)
@@ -288,7 +288,7 @@ void launch_apply(const Model& m, int precision, int nb, const void* V, int64_t 
                   hipStream_t s);
 // One-body jump lists of one species, generated on the device (jumps.hip): counts per
 // (determinant, class) [g * ncl + c], the lists written at given starts and sorted, the proton
-// jump groups, and the packed neutron forms.
+// jump groups, and the packed neutron form.
 class JumpTables {
  public:
   JumpTables(const Model& m, int s);
@@ -299,7 +299,7 @@ class JumpTables {
   std::vector<int> group_counts(const DevBuf& start, const DevBuf& jidx);
   void group_fill(const DevBuf& start, const DevBuf& jidx, const DevBuf& gstart, int ngroups, DevBuf& gdesc,
                   DevBuf& cend);
-  void pack(const DevBuf& jidx, const DevBuf& jmeta, int64_t n, DevBuf& pack, DevBuf& p32);
+  void pack(const DevBuf& jidx, const DevBuf& jmeta, int64_t n, DevBuf& p32);
 
  private:
   const Model& m_;

@@ -120,13 +120,11 @@ __global__ void group_kernel(int nsd, int ncl, const int* start, const int* jidx
   }
 }
 
-// Neutron jumps packed for the kernels: (source, op << 1 | sign) pairs, and one word
-// sign << 31 | op << 16 | source
-__global__ void pack_kernel(int64_t n, const int* jidx, const int* jmeta, int2* pack, uint32_t* p32) {
+// Neutron jumps packed for the rows kernel: one word sign << 31 | op << 16 | source
+__global__ void pack_kernel(int64_t n, const int* jidx, const int* jmeta, uint32_t* p32) {
   const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (q >= n) return;
   const int i = jidx[q], m = jmeta[q];
-  pack[q] = make_int2(i, m);
   p32[q] = ((uint32_t)(m & 1) << 31) | ((uint32_t)(m >> 1) << 16) | (uint32_t)i;
 }
 
@@ -200,13 +198,12 @@ void JumpTables::group_fill(const DevBuf& start, const DevBuf& jidx, const DevBu
   TRBL_HIP(hipGetLastError());
 }
 
-void JumpTables::pack(const DevBuf& jidx, const DevBuf& jmeta, int64_t n, DevBuf& pack, DevBuf& p32) {
-  pack.alloc((size_t)std::max<int64_t>(n, 1) * sizeof(int2));
+void JumpTables::pack(const DevBuf& jidx, const DevBuf& jmeta, int64_t n, DevBuf& p32) {
   p32.alloc((size_t)(n + 32) * sizeof(uint32_t));  // register loads read up to 32 past a list
   TRBL_HIP(hipMemset(p32.p, 0, (size_t)(n + 32) * sizeof(uint32_t)));
   if (n > 0)
     hipLaunchKernelGGL(pack_kernel, dim3(blocks_for(n)), dim3(256), 0, 0, n, jidx.as<int>(), jmeta.as<int>(),
-                       pack.as<int2>(), p32.as<uint32_t>());
+                       p32.as<uint32_t>());
   TRBL_HIP(hipGetLastError());
 }
 

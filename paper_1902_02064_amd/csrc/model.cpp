@@ -421,15 +421,13 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
     const std::vector<double>& e1 = m.spe[s];
     std::vector<int> ptr(1, 0), col;
     std::vector<double> val;
-    std::vector<int> tptr(1, 0), tid;  // gradient: per entry, contributing (term, sign)
-    std::vector<int8_t> tsg;
-    std::vector<std::pair<int, std::pair<double, std::pair<int, int>>>> row;  // (g, (h, (term, sign)))
+    std::vector<std::pair<int, double>> row;  // (g, h)
     for (int g = 0; g < (int)S.words.size(); g++) {
       uint64_t w = S.words[g];
       row.clear();
       double diag = 0.0;
       for (uint64_t x = w; x; x &= x - 1) diag += e1[m.st_orb[__builtin_ctzll(x)]];
-      row.push_back({g, {diag, {-1, 0}}});
+      row.push_back({g, diag});
       for (uint64_t x = w; x; x &= x - 1) {
         int a = __builtin_ctzll(x);
         for (uint64_t y = x & (x - 1); y; y &= y - 1) {
@@ -449,7 +447,7 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
             r |= 1ull << t.c;
             auto it = S.index.find(r);
             if (it == S.index.end()) continue;
-            row.push_back({it->second, {t.h * sg, {k, sg}}});
+            row.push_back({it->second, t.h * sg});
           }
         }
       }
@@ -459,21 +457,15 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
         size_t j = i;
         double h = 0.0;
         while (j < row.size() && row[j].first == row[i].first) {
-          h += row[j].second.first;
-          if (row[j].second.second.first >= 0) {
-            tid.push_back(row[j].second.second.first);
-            tsg.push_back((int8_t)row[j].second.second.second);
-          }
+          h += row[j].second;
           j++;
         }
         col.push_back(row[i].first - base);
         val.push_back(h);
-        tptr.push_back((int)tid.size());
         i = j;
       }
       ptr.push_back((int)col.size());
     }
-    std::vector<float> val32(val.begin(), val.end());
     // Lane order of the rows kernel inside each neutron sector: SDs sorted by their number of
     // one-body jumps in each class (the class of no change first, then outwards), so that the
     // 64 targets of a wavefront have similar jump counts and few lanes idle while the longest
@@ -549,13 +541,6 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
       (s == 0 ? m.dt.pe_v32 : m.dt.ne_v32).upload(eval32);
       m.sec_slice0[s] = sec_slice0;
     }
-    (s == 0 ? m.dt.pp_ptr : m.dt.nn_ptr).upload(ptr);
-    (s == 0 ? m.dt.pp_col : m.dt.nn_col).upload(col);
-    (s == 0 ? m.dt.pp_v64 : m.dt.nn_v64).upload(val);
-    (s == 0 ? m.dt.pp_v32 : m.dt.nn_v32).upload(val32);
-    (s == 0 ? m.dt.pp_tptr : m.dt.nn_tptr).upload(tptr);
-    (s == 0 ? m.dt.pp_tid : m.dt.nn_tid).upload(tid);
-    (s == 0 ? m.dt.pp_tsgn : m.dt.nn_tsgn).upload(tsg);
   }
 
   {
@@ -576,7 +561,6 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
     hoff[c + 1] = hoff[c] + (int)pops[c].size() * hncol[c];
   }
   std::vector<double> h(hoff[ncl], 0.0);
-  std::vector<int> hterm(hoff[ncl], -1);
   for (int k = 0; k < (int)m.terms_pn.size(); k++) {
     const MTerm& t = m.terms_pn[k];  // c+_a(p) c+_b(n) c_d(n) c_c(p): proton op (a,c), neutron op (b,d)
     const int c = op_cls[t.a * ns + t.c];
@@ -584,17 +568,13 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
     TRBL_REQUIRE(cn == cl.conj(c), TRBL_E_INVALID, "pn term breaks M or parity conservation");
     const int at = hoff[c] + op_idx[t.a * ns + t.c] * hncol[c] + op_idx[t.b * ns + t.d];
     h[at] += t.h;
-    hterm[at] = k;
   }
-  m.h_off_host = hoff;
-  m.h_ncol_host = hncol;
   m.max_hncol = *std::max_element(hncol.begin(), hncol.end());
   std::vector<float> h32(h.begin(), h.end());
   m.dt.h_off.upload(hoff);
   m.dt.h_ncol.upload(hncol);
   m.dt.h64.upload(h);
   m.dt.h32.upload(h32);
-  m.dt.h_term.upload(hterm);
   // Jump lists (device, jumps.hip): from each SD g' remove x in g', add y not in g' \ {x}
   // (y == x allowed). Proton side: per (SD, class), sorted by source index so equal source rows
   // are adjacent. Neutron side: class-major, so the lists of consecutive SDs in one class are
@@ -647,7 +627,7 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
       for (const auto& v : pops) maxops = std::max(maxops, (int)v.size());
       TRBL_REQUIRE(maxsec <= 65536 && maxops <= 32768, TRBL_E_INVALID,
                    "neutron sector or operator class too large for the packed jump lists");
-      jt[1].pack(jidx, jmeta, total, m.dt.nj_pack, m.dt.nj32);
+      jt[1].pack(jidx, jmeta, total, m.dt.nj32);
       for (int x : cnt) mx = std::max(mx, x);
       m.max_nj_class = mx;
     } else {
