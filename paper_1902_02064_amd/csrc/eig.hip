@@ -2,7 +2,7 @@
 // "diagonalise T^(k)"; restart equations of Sec. 3.4), FP64, in five launches:
 //
 //   1. Householder reduction to tridiagonal form (A = Q Tri Q^T), reflectors kept
-//      (one workgroup: every step depends on the previous one);
+//      (every step depends on the previous one: one workgroup up to n = 128, several beyond);
 //   2. eigenvalues by Sturm-sequence multisection, a group of threads per wanted index,
 //      spread over workgroups;
 //   3. eigenvectors of Tri by inverse iteration with a pivoted LU of (Tri - lambda I),
@@ -14,6 +14,7 @@
 // Textbook methods (Householder; Sturm-sequence bisection; inverse iteration),
 // written for this library.
 #include <cfloat>
+#include <type_traits>
 
 #include <hip/hip_cooperative_groups.h>
 
@@ -36,9 +37,32 @@ __device__ static double block_sum(double v, double* red) {
   return s;
 }
 
-__device__ static double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// v moved by a DPP control inside rows of 16 lanes
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
+// sum of 4 consecutive lanes, in each of them
+__device__ __forceinline__ double quad_sum(double v) {
+  v += dpp<0xB1>(v);     // quad_perm [1,0,3,2]
+  return v + dpp<0x4E>(v);  // quad_perm [2,3,0,1]
+}
+
+// sum over the wavefront, in every lane: DPP inside the rows, the four rows through scalar registers
+// (a butterfly of LDS permutes takes about three times as long, and these sums lie on serial chains)
+__device__ __forceinline__ double wave_sum(double v) {
+  v = quad_sum(v);
+  v += dpp<0x141>(v);  // row_half_mirror
+  v += dpp<0x140>(v);  // row_mirror
+  double s[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++)
+    s[r] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 16 * r),
+                            __builtin_amdgcn_readlane(__double2loint(v), 16 * r));
+  return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 __device__ static uint64_t mix64(uint64_t z) {
@@ -48,21 +72,99 @@ __device__ static uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
+// 1 / q to working accuracy for normal q with a normal reciprocal: the hardware estimate and two Newton
+// steps (a third of the latency of a division, which is the whole chain of a Sturm count)
+__device__ __forceinline__ double recip(double q) {
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(fma(-q, r, 1.0), r, r);
+  return fma(fma(-q, r, 1.0), r, r);
+}
+
+// 1 / sqrt(q) the same way
+__device__ __forceinline__ double rsqrt2(double q) {
+  double r = __builtin_amdgcn_rsq(q);
+  r = fma(0.5 * r, fma(-q * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-q * r, r, 1.0), r);
+}
+
 // number of eigenvalues of the tridiagonal (d, e2 = squared off-diagonal) below x
 __device__ static int sturm(const double* d, const double* e2, int n, double x, double pivmin) {
   int cnt = 0;
   double q = d[0] - x;
   if (fabs(q) <= pivmin) q = -pivmin;
   if (q < 0.0) cnt++;
-  for (int i = 1; i < n; i++) {
-    q = d[i] - x - e2[i - 1] / q;
-    if (fabs(q) <= pivmin) q = -pivmin;
-    if (q < 0.0) cnt++;
-  }
+  auto run = [&](int i0, auto len) {  // len entries whose LDS reads are issued together
+    constexpr int U = decltype(len)::value;
+    double dx[U], f[U];
+#pragma unroll
+    for (int t = 0; t < U; t++) {
+      dx[t] = d[i0 + t] - x;
+      f[t] = e2[i0 + t - 1];
+    }
+#pragma unroll
+    for (int t = 0; t < U; t++) {
+      q = fma(-f[t], recip(q), dx[t]);
+      q = fabs(q) <= pivmin ? -pivmin : q;
+      cnt += q < 0.0 ? 1 : 0;
+    }
+  };
+  int i = 1;
+  for (; i + 8 <= n; i += 8) run(i, std::integral_constant<int, 8>{});
+  for (; i < n; i++) run(i, std::integral_constant<int, 1>{});
   return cnt;
 }
 
 constexpr int EIG_BIG = 20 * EIG_NMAX;  // shared work area (doubles)
+
+// d, e (LDS) and the spectrum's bounds to de (see tridiag_kernel)
+__device__ static void tri_finish(int n, const double* d, const double* e, double* __restrict__ de) {
+  __shared__ double wlo[16], whi[16], wnm[16];
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6, nwave = nthr >> 6;
+  __syncthreads();
+  // Gershgorin interval and a norm bound
+  double glo = 1e300, ghi = -1e300, gn = 0.0;
+  for (int i = tid; i < n; i += nthr) {
+    const double r = fabs(e[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0);
+    glo = fmin(glo, d[i] - r);
+    ghi = fmax(ghi, d[i] + r);
+    gn = fmax(gn, fabs(d[i]) + r);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    glo = fmin(glo, __shfl_down(glo, o, 64));
+    ghi = fmax(ghi, __shfl_down(ghi, o, 64));
+    gn = fmax(gn, __shfl_down(gn, o, 64));
+  }
+  if (lane == 0) {
+    wlo[wave] = glo;
+    whi[wave] = ghi;
+    wnm[wave] = gn;
+  }
+  __syncthreads();
+  glo = 1e300;
+  ghi = -1e300;
+  gn = 0.0;
+  for (int w = 0; w < nwave; w++) {
+    glo = fmin(glo, wlo[w]);
+    ghi = fmax(ghi, whi[w]);
+    gn = fmax(gn, wnm[w]);
+  }
+  const double tnorm = fmax(gn, DBL_MIN);
+  // smallest pivot of a Sturm count: far below every rounding, and e^2 / pivmin stays finite
+  const double pivmin = fmax(1e-150 * tnorm, 1e-290);
+  glo -= 2.0 * DBL_EPSILON * tnorm * n + pivmin;
+  ghi += 2.0 * DBL_EPSILON * tnorm * n + pivmin;
+  for (int i = tid; i < n; i += nthr) {
+    de[i] = d[i];
+    de[n + i] = e[i];
+    de[2 * n + i] = e[i] * e[i];
+  }
+  if (tid == 0) {
+    de[3 * n] = glo;
+    de[3 * n + 1] = ghi;
+    de[3 * n + 2] = tnorm;
+    de[3 * n + 3] = pivmin;
+  }
+}
 
 // Householder reduction to tridiagonal form, unblocked, on ceil(n / TRI_RW) cooperating
 // workgroups of 256 threads. Workgroup g holds rows [g TRI_RW, (g+1) TRI_RW) of the current
@@ -80,11 +182,10 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const double* __restrict__
                                                       double* __restrict__ A, double* __restrict__ de,
                                                       double* __restrict__ xb) {
   extern __shared__ double lds[];
-  __shared__ double d[EIG_NMAX], e[EIG_NMAX], e2[EIG_NMAX];
-  __shared__ double red[32], wlo[16], whi[16], wnm[16];
+  __shared__ double d[EIG_NMAX], e[EIG_NMAX];
+  __shared__ double red[32];
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int lane = tid & 63, wave = tid >> 6, nwave = nthr >> 6;
   const int g = blockIdx.x, r0 = g * TRI_RW, nr = min(TRI_RW, n - r0);
   double* Ar = lds;              // nr x n, own rows
   double* v = Ar + TRI_RW * n;   // reflector
@@ -158,208 +259,355 @@ __global__ __launch_bounds__(256) void tridiag_kernel(const double* __restrict__
     d[n - 1] = xl[0];
     e[n - 1] = 0.0;
   }
-  __syncthreads();
-  for (int i = tid; i < n; i += nthr) e2[i] = e[i] * e[i];
-  // Gershgorin interval and a norm bound
-  double glo = 1e300, ghi = -1e300, gn = 0.0;
-  for (int i = tid; i < n; i += nthr) {
-    const double r = fabs(e[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0);
-    glo = fmin(glo, d[i] - r);
-    ghi = fmax(ghi, d[i] + r);
-    gn = fmax(gn, fabs(d[i]) + r);
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    glo = fmin(glo, __shfl_down(glo, o, 64));
-    ghi = fmax(ghi, __shfl_down(ghi, o, 64));
-    gn = fmax(gn, __shfl_down(gn, o, 64));
-  }
-  if (lane == 0) {
-    wlo[wave] = glo;
-    whi[wave] = ghi;
-    wnm[wave] = gn;
-  }
-  __syncthreads();
-  glo = 1e300;
-  ghi = -1e300;
-  gn = 0.0;
-  for (int w = 0; w < nwave; w++) {
-    glo = fmin(glo, wlo[w]);
-    ghi = fmax(ghi, whi[w]);
-    gn = fmax(gn, wnm[w]);
-  }
-  const double tnorm = fmax(gn, DBL_MIN);
-  const double pivmin = DBL_MIN * fmax(1.0, tnorm * tnorm);
-  glo -= 2.0 * DBL_EPSILON * tnorm * n + pivmin;
-  ghi += 2.0 * DBL_EPSILON * tnorm * n + pivmin;
-  for (int i = tid; i < n; i += nthr) {
-    de[i] = d[i];
-    de[n + i] = e[i];
-    de[2 * n + i] = e2[i];
-  }
-  if (tid == 0) {
-    de[3 * n] = glo;
-    de[3 * n + 1] = ghi;
-    de[3 * n + 2] = tnorm;
-    de[3 * n + 3] = pivmin;
-  }
+  tri_finish(n, d, e, de);
 }
 
+// sum of the 16 lanes of a row, in each of them
+__device__ __forceinline__ double row_sum(double v) {
+  v = quad_sum(v);
+  v += dpp<0x141>(v);  // row_half_mirror
+  return v + dpp<0x140>(v);  // row_mirror
+}
 
-// eigenvalues by multisection: a group of BIS_TPE threads refines one eigenvalue (the nvec
-// lowest and the largest); each round its threads take Sturm counts at BIS_TPE interior points
-// of the group's interval, which shrinks by a factor BIS_TPE + 1. Launch: 256 threads per
-// workgroup, ceil((nvec + 1) * BIS_TPE / 256) workgroups.
-constexpr int BIS_TPE = 32;
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// LDS accesses of the lanes of one wavefront across this point happen in order (they are issued and
+// complete in order; this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same reduction for n <= TS on one workgroup, the matrix in registers: a thread holds the rows
+// tid / 16 + 16 i and columns tid % 16 + 16 k. A step costs one barrier: every wavefront holds row j in its
+// lanes and forms the reflector v by itself; the products p = A v (summed over 16 lanes), the shares of
+// v^T p and row j + 1 as it stands are published; after the barrier every wavefront forms w and row
+// j + 1 for itself, and the threads update their elements. v is zero in finished rows and columns: their
+// remainder is only reflected from one side, which needs no masks. The exchange area alternates between
+// two halves. The serial chain of a step bounds it (a taken branch costs as much as ten of its
+// operations), so there are next to none, one wavefront per SIMD, and a smaller instance for n <= 64.
+// Over a run's calls: n up to 112 142 us against 450 us on seven workgroups with a grid barrier per step,
+// n = 20 to 56 38 us against 138 us. (With the matrix in LDS 280 and 61 us, on 512 threads 205 and 63 us.)
+constexpr int TRI_SMALL = 128;
+template <int TS>
+__global__ __launch_bounds__(256) void tridiag_small_kernel(const double* __restrict__ T, int ldt, int n,
+                                                            double* __restrict__ A, double* __restrict__ de) {
+  constexpr int NW = 4, NX = TS / 64, NB = TS / 16;
+  __shared__ double d[TS], e[TS];
+  __shared__ double pv[2][TS], xr[2][TS], kp[2][NW];
+  __shared__ double vw[NW][2][TS];  // v and w of each wavefront
+  __shared__ double last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cg = tid & 15, rg = tid >> 4;
+  double* const v = vw[wave][0];
+  double* const w = vw[wave][1];
+  double a[NB][NB], x[NX], vl[NX];
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int k = 0; k < NB; k++) {
+      const int r = rg + 16 * i, c = cg + 16 * k;
+      const double t = T[(int64_t)min(r, n - 1) * ldt + min(c, n - 1)];
+      a[i][k] = r < n && c < n ? t : 0.0;
+    }
+#pragma unroll
+  for (int i = 0; i < NX; i++) {
+    const double t = T[min(lane + 64 * i, n - 1)];
+    x[i] = lane + 64 * i < n ? t : 0.0;
+  }
+  // one step on the blocks [LO, NB) of 16 rows and columns
+  auto step = [&](int j, auto lo) {
+    constexpr int LO = decltype(lo)::value, LX = LO / 4;
+    const int h = j & 1;
+    double s = 0.0;
+#pragma unroll
+    for (int i = LX; i < NX; i++) s += lane + 64 * i > j ? x[i] * x[i] : 0.0;
+    const double s2 = wave_sum(s);
+    const double x0 = lane_value(LX == 0 && j < 63 ? x[0] : x[NX - 1], (j + 1) & 63);
+    // |x - alpha e_1|^2 = 2 (s2 + |x0| sigma); the square roots and the division by reciprocal roots
+    // (estimate and two Newton steps)
+    const bool zero = s2 < 1e-280;
+    const double sigma = zero ? 0.0 : s2 * rsqrt2(s2);
+    const double alpha = (x0 > 0.0) ? -sigma : sigma;
+    const double vn = zero ? 0.0 : rsqrt2(2.0 * (s2 + fabs(x0) * sigma));
+    const double vj = (x0 - alpha) * vn;
+#pragma unroll
+    for (int i = LX; i < NX; i++) {
+      const int c = lane + 64 * i;
+      vl[i] = c <= j ? 0.0 : c == j + 1 ? vj : x[i] * vn;
+      v[c] = vl[i];
+    }
+    if (wave == 0) {
+#pragma unroll
+      for (int i = LX; i < NX; i++) {
+        const int c = lane + 64 * i;
+        if (c < n) A[(int64_t)j * n + c] = vl[i];  // zeros up to column j
+        if (c == j) {
+          d[j] = x[i];
+          e[j] = alpha;
+        }
+      }
+    }
+    wave_sync();
+    double vc[NB], vr[NB], t[NB], ks = 0.0;
+#pragma unroll
+    for (int k = LO; k < NB; k++) {
+      vc[k] = v[cg + 16 * k];
+      vr[k] = v[rg + 16 * k];
+      t[k] = 0.0;
+    }
+#pragma unroll
+    for (int k = LO; k < NB; k++)
+#pragma unroll
+      for (int i = LO; i < NB; i++) t[i] = fma(a[i][k], vc[k], t[i]);
+#pragma unroll
+    for (int i = LO; i < NB; i++) {
+      t[i] = row_sum(t[i]);
+      ks = fma(vr[i], t[i], ks);
+    }
+    if (cg == 0) {
+#pragma unroll
+      for (int i = LO; i < NB; i++) pv[h][rg + 16 * i] = t[i];
+    }
+    if (rg == ((j + 1) & 15)) {
+      double y[NB] = {};  // (a selection by ?: would put the matrix into scratch memory)
+#pragma unroll
+      for (int i = LO; i < NB; i++) {
+        const double m = (j + 1) >> 4 == i ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = LO; k < NB; k++) y[k] = fma(m, a[i][k], y[k]);
+      }
+#pragma unroll
+      for (int k = LO; k < NB; k++) xr[h][cg + 16 * k] = y[k];
+    }
+    const double k1 = (lane_value(ks, 0) + lane_value(ks, 16)) + (lane_value(ks, 32) + lane_value(ks, 48));
+    if (lane == 0) kp[h][wave] = k1;
+    __syncthreads();
+    const double K = (kp[h][0] + kp[h][1]) + (kp[h][2] + kp[h][3]);
+    const double wj = 2.0 * fma(-K, vj, pv[h][j + 1]);
+#pragma unroll
+    for (int i = LX; i < NX; i++) {
+      const int c = lane + 64 * i;
+      const double wl = 2.0 * fma(-K, vl[i], pv[h][c]);
+      w[c] = wl;
+      x[i] = fma(-vj, wl, fma(-wj, vl[i], xr[h][c]));
+    }
+    wave_sync();
+    double wr[NB], wc[NB];
+#pragma unroll
+    for (int i = LO; i < NB; i++) {
+      wr[i] = w[rg + 16 * i];
+      wc[i] = w[cg + 16 * i];
+    }
+#pragma unroll
+    for (int k = LO; k < NB; k++)
+#pragma unroll
+      for (int i = LO; i < NB; i++) a[i][k] = fma(-vr[i], wc[k], fma(-wr[i], vc[k], a[i][k]));
+    wave_sync();
+  };
+  int j = 0;
+  for (; j + 2 < n && j < 64; j++) step(j, std::integral_constant<int, 0>{});
+  if (NB > 4)
+    for (; j + 2 < n; j++) step(j, std::integral_constant<int, NB - 4>{});
+  // the last two rows: row n - 2 is in x, the last diagonal element with its owner
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+    if (rg + 16 * i == n - 1 && cg == rg) last = a[i][i];
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int i = 0; i < NX; i++) {
+      const int c = lane + 64 * i;
+      if (n >= 2 && c == n - 2) d[c] = x[i];
+      if (n >= 2 && c == n - 1) e[n - 2] = x[i];
+    }
+    if (lane == 0) {
+      d[n - 1] = last;
+      e[n - 1] = 0.0;
+    }
+  }
+  tri_finish(n, d, e, de);
+}
+
+// eigenvalues by multisection: a group of TPE threads refines one eigenvalue (the nvec lowest and the
+// largest); each round its threads take Sturm counts at TPE interior points of the group's interval, which
+// shrinks by a factor TPE + 1. Launch: 256 threads per workgroup, ceil((nvec + 1) TPE / 256) workgroups.
+// A round is one serial Sturm chain whatever TPE is, so a whole workgroup per eigenvalue (9 rounds) is
+// taken while that fills no more than the chip, else 32 threads (14 rounds). n = 20 to 56: 18 us a call,
+// 43 us with 32 threads each and a division per step of the chain.
+template <int TPE>
 __global__ __launch_bounds__(256) void bisect_kernel(const double* __restrict__ de, int n, int nvec,
                                                      double* __restrict__ theta) {
   __shared__ double d[EIG_NMAX], e2[EIG_NMAX];
-  __shared__ double sx[256];
-  __shared__ int scnt[256];
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  for (int i = tid; i < n; i += nthr) {
+  __shared__ uint64_t above[4];  // per wavefront: points with more eigenvalues below than wanted
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int i = tid; i < n; i += 256) {
     d[i] = de[i];
     e2[i] = de[2 * n + i];
   }
-  double glo = de[3 * n], ghi = de[3 * n + 1];
+  double lo = de[3 * n], hi = de[3 * n + 1];
   const double pivmin = de[3 * n + 3];
   __syncthreads();
-  {
-    const int tpe = BIS_TPE;
-    const int q = blockIdx.x * (nthr / tpe) + tid / tpe, sub = tid % tpe;
-    const int want = q < nvec ? q : ((q == nvec && nvec < n) ? n - 1 : -1);
-    double lo = glo, hi = ghi;
-    const int rounds = (int)ceil(64.0 / log2((double)tpe + 1.0)) + 1;
-    for (int rd = 0; rd < rounds; rd++) {
-      const bool live =
-          want >= 0 && !(hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 2.0 * pivmin);
-      double x = lo;
-      int cnt = -1;
-      if (live) {
-        x = lo + (hi - lo) * (double)(sub + 1) / (double)(tpe + 1);
-        cnt = sturm(d, e2, n, x, pivmin);
-      }
-      sx[tid] = x;
-      scnt[tid] = cnt;
+  const int q = blockIdx.x * (256 / TPE) + tid / TPE, sub = tid % TPE;
+  const int want = q < nvec ? q : ((q == nvec && nvec < n) ? n - 1 : -1);
+  const int rounds = TPE == 256 ? 9 : 14;  // 64 bits at log2(TPE + 1) a round, and one more
+  for (int rd = 0; rd < rounds; rd++) {
+    const bool live = want >= 0 && !(hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 2.0 * pivmin);
+    const double step = (hi - lo) / (double)(TPE + 1);
+    const bool up = live && sturm(d, e2, n, lo + step * (double)(sub + 1), pivmin) > want;
+    const uint64_t b = __ballot(up);
+    int first;  // first point of the group above the eigenvalue
+    if constexpr (TPE == 256) {
+      if (lane == 0) above[wave] = b;
       __syncthreads();
-      if (live) {
-        double nlo = lo, nhi = hi;
-        for (int t = 0; t < tpe; t++) {
-          const double xt = sx[(tid / tpe) * tpe + t];
-          if (scnt[(tid / tpe) * tpe + t] > want) nhi = fmin(nhi, xt);
-          else nlo = fmax(nlo, xt);
-        }
-        lo = nlo;
-        hi = nhi;
-      }
+      first = 256;
+      for (int w = 3; w >= 0; w--)
+        if (above[w]) first = 64 * w + __builtin_ctzll(above[w]);
       __syncthreads();
+    } else {
+      const uint32_t g = (uint32_t)(b >> (lane & 32));
+      first = g ? __builtin_ctz(g) : TPE;
     }
-    if (want >= 0 && sub == 0) theta[want] = 0.5 * (lo + hi);
+    if (live) {
+      const double nhi = first < TPE ? lo + step * (double)(first + 1) : hi;
+      if (first > 0) lo = lo + step * (double)first;
+      hi = nhi;
+    }
   }
+  if (want >= 0 && sub == 0) theta[want] = 0.5 * (lo + hi);
 }
 
 // inverse iteration, one thread per wanted vector. The pivoted LU of (Tri - lambda I) is
 // computed with the running pivot row kept in registers and written out once to LDS; the
 // solves stream through it. Column j of Z (row-major, stride nvec) receives vector j.
+// One serial chain of seven passes over n entries bounds it, so it holds nothing but that chain: the start
+// vectors and the results are written by all lanes, the scaling of an iterate is left to the next pass that
+// reads it, and a pass takes U entries at a time, whose LDS reads are issued together ahead of the
+// arithmetic; no branch inside (26 us at n = 64, 52 us with the tests of a ragged end in the loops).
 // Launch: ceil(nvec / INV_VPW) workgroups of 64 threads, 2 n + INV_VPW (6 n + 4) doubles of LDS.
 constexpr int INV_VPW = 4;
 __global__ __launch_bounds__(64) void inviter_kernel(const double* __restrict__ de, const double* __restrict__ theta,
                                                      int n, int nvec, double* __restrict__ Z) {
+  constexpr int U = 4;
   extern __shared__ double lds[];
-  const int tid = threadIdx.x;
+  __shared__ double scale[INV_VPW];
+  const int tid = threadIdx.x, j0 = blockIdx.x * INV_VPW, nv = min(INV_VPW, nvec - j0);
   double* d = lds;
   double* e = lds + n;
-  for (int i = tid; i < n; i += blockDim.x) {
+  double* const lu = lds + 2 * n;  // per vector, padded against bank conflicts
+  const int ldl = 6 * n + 4;
+  for (int i = tid; i < n; i += 64) {
     d[i] = de[i];
     e[i] = de[n + i];
   }
+  for (int q = tid; q < n * nv; q += 64) {
+    const int jl = q / n, i = q - jl * n;
+    const uint64_t h = mix64(mix64(0x5D0C5EEDull + (uint64_t)(j0 + jl) * 1315423911ull) + i);
+    lu[jl * ldl + 5 * n + i] = ((double)(h >> 11) * (1.0 / 9007199254740992.0)) - 0.5;
+  }
   const double tnorm = de[3 * n + 2];
   __syncthreads();
-  {
-    const int jl = tid;
-    const int j = blockIdx.x * INV_VPW + jl;
-    if (jl >= INV_VPW || j >= nvec) return;
-    double* dl = lds + 2 * n + (int64_t)jl * (6 * n + 4);  // padded against bank conflicts
+  if (tid < nv) {
+    double* dl = lu + tid * ldl;
     double* dd = dl + n;
     double* du = dd + n;
     double* du2 = du + n;
     double* pv = du2 + n;
-    double* zl = pv + n;
-#define AT(p, i) (p)[(i)]
-    const double lm = theta[j];
-    const double tiny = DBL_EPSILON * tnorm;
-    // running values of the current pivot row: a = dd[i], u1 = du[i]
+    double* z = pv + n;
+    const double lm = theta[j0 + tid];
+    const double tiny = fmax(DBL_EPSILON * tnorm, 1e-290);
+    // running values of the current pivot row: a = pivot, u1 = superdiagonal
     double a = d[0] - lm, u1 = e[0];
-    for (int i = 0; i + 1 < n; i++) {
-      const double b = e[i];                  // sub-diagonal below the pivot
-      const double dnext = d[i + 1] - lm, enext = (i + 2 < n) ? e[i + 1] : 0.0;
-      double piv, sup, sup2, mult, na, nu1;
-      bool sw;
-      if (fabs(a) >= fabs(b)) {
-        sw = false;
-        piv = a;
-        sup = u1;
-        sup2 = 0.0;
-        mult = (a != 0.0) ? b / a : 0.0;
-        na = dnext - mult * u1;
-        nu1 = enext;
-      } else {
-        sw = true;
-        piv = b;
-        sup = dnext;
-        sup2 = enext;
-        mult = a / b;
-        na = u1 - mult * dnext;
-        nu1 = -mult * enext;
+    auto factor = [&](int i0, auto cnt) {
+      constexpr int U = decltype(cnt)::value;
+      double dn[U], en[U + 1];
+#pragma unroll
+      for (int t = 0; t < U; t++) dn[t] = d[i0 + t + 1] - lm;
+#pragma unroll
+      for (int t = 0; t <= U; t++) en[t] = e[i0 + t];  // e[n - 1] = 0
+#pragma unroll
+      for (int t = 0; t < U; t++) {
+        const int i = i0 + t;
+        const double b = en[t];  // sub-diagonal below the pivot
+        const bool sw = !(fabs(a) >= fabs(b));
+        double piv = sw ? b : a;
+        piv = fabs(piv) < tiny ? copysign(tiny, piv) : piv;
+        const double rp = recip(piv);
+        const double mult = (sw ? a : b) * rp;
+        const double sup = sw ? dn[t] : u1, sup2 = sw ? en[t + 1] : 0.0;
+        a = fma(-mult, sup, sw ? u1 : dn[t]);
+        u1 = sw ? -mult * en[t + 1] : en[t + 1];
+        dd[i] = rp;
+        du[i] = sup;
+        du2[i] = sup2;
+        dl[i] = mult;
+        pv[i] = sw ? 1.0 : 0.0;
       }
-      if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
-      AT(dd, i) = piv;
-      AT(du, i) = sup;
-      AT(du2, i) = sup2;
-      AT(dl, i) = mult;
-      AT(pv, i) = sw ? 1.0 : 0.0;
-      a = na;
-      u1 = nu1;
-    }
-    if (fabs(a) < tiny) a = (a < 0.0) ? -tiny : tiny;
-    AT(dd, n - 1) = a;
-    AT(du, n - 1) = 0.0;
-    AT(du2, n - 1) = 0.0;
-    double* z = zl;
-    uint64_t h = mix64(0x5D0C5EEDull + (uint64_t)j * 1315423911ull);
-    for (int i = 0; i < n; i++) {
-      h = mix64(h + i);
-      AT(z, i) = ((double)(h >> 11) * (1.0 / 9007199254740992.0)) - 0.5;
-    }
+    };
+    int i = 0;
+    for (; i + U < n; i += U) factor(i, std::integral_constant<int, U>{});
+    for (; i + 1 < n; i++) factor(i, std::integral_constant<int, 1>{});
+    a = fabs(a) < tiny ? copysign(tiny, a) : a;
+    dd[n - 1] = recip(a);
+    double sc = 1.0;
     for (int it = 0; it < 3; it++) {
       // forward: row interchanges and L, with the two live entries in registers
-      double zc = AT(z, 0);
-      for (int i = 0; i + 1 < n; i++) {
-        double zn = AT(z, i + 1);
-        if (AT(pv, i) != 0.0) {
-          const double t = zc;
-          zc = zn;
-          zn = t;
+      double zc = z[0] * sc;
+      auto forward = [&](int i0, auto cnt) {
+        constexpr int U = decltype(cnt)::value;
+        double zn[U], m[U], p[U];
+#pragma unroll
+        for (int t = 0; t < U; t++) {
+          zn[t] = z[i0 + t + 1];
+          m[t] = dl[i0 + t];
+          p[t] = pv[i0 + t];
         }
-        AT(z, i) = zc;
-        zc = zn - AT(dl, i) * zc;
-      }
-      AT(z, n - 1) = zc;
+#pragma unroll
+        for (int t = 0; t < U; t++) {
+          zn[t] *= sc;
+          const double top = p[t] != 0.0 ? zn[t] : zc, bot = p[t] != 0.0 ? zc : zn[t];
+          z[i0 + t] = top;
+          zc = fma(-m[t], top, bot);
+        }
+      };
+      for (i = 0; i + U < n; i += U) forward(i, std::integral_constant<int, U>{});
+      for (; i + 1 < n; i++) forward(i, std::integral_constant<int, 1>{});
       // backward: U, carrying z[i+1], z[i+2]
-      double z1 = AT(z, n - 1) / AT(dd, n - 1), z2 = 0.0;
-      AT(z, n - 1) = z1;
-      for (int i = n - 2; i >= 0; i--) {
-        const double zi = (AT(z, i) - AT(du, i) * z1 - AT(du2, i) * z2) / AT(dd, i);
-        AT(z, i) = zi;
-        z2 = z1;
-        z1 = zi;
-      }
-      double nr = 0.0;
-      for (int i = 0; i < n; i++) nr += AT(z, i) * AT(z, i);
-      nr = 1.0 / sqrt(nr);
-      for (int i = 0; i < n; i++) AT(z, i) *= nr;
+      double z1 = zc * dd[n - 1], z2 = 0.0, nr = z1 * z1;
+      z[n - 1] = z1;
+      auto backward = [&](int i0, auto cnt) {  // entries i0, i0 - 1, ..
+        constexpr int U = decltype(cnt)::value;
+        double zi[U], u[U], uu[U], r[U];
+#pragma unroll
+        for (int t = 0; t < U; t++) {
+          zi[t] = z[i0 - t];
+          u[t] = du[i0 - t];
+          uu[t] = du2[i0 - t];
+          r[t] = dd[i0 - t];
+        }
+#pragma unroll
+        for (int t = 0; t < U; t++) {
+          const double x = fma(-u[t], z1, fma(-uu[t], z2, zi[t])) * r[t];
+          nr = fma(x, x, nr);
+          z2 = z1;
+          z1 = x;
+          z[i0 - t] = x;
+        }
+      };
+      for (i = n - 2; i + 1 >= U; i -= U) backward(i, std::integral_constant<int, U>{});
+      for (; i >= 0; i--) backward(i, std::integral_constant<int, 1>{});
+      sc = 1.0 / sqrt(nr);
     }
-#undef AT
-    for (int i = 0; i < n; i++) Z[(int64_t)i * nvec + j] = zl[i];
+    scale[tid] = sc;
+  }
+  __syncthreads();
+  for (int q = tid; q < n * nv; q += 64) {
+    const int i = q / nv, jl = q - i * nv;
+    Z[(int64_t)i * nvec + j0 + jl] = lu[jl * ldl + 5 * n + i] * scale[jl];
   }
 }
 
@@ -463,7 +711,9 @@ __global__ __launch_bounds__(256) void rsolve_kernel(int n, int nvec, double* __
 
 // back-transformation U = H_0 H_1 ... H_{n-3} Z (reflectors applied last to first): one
 // workgroup per block of 16 columns, held in LDS, one wave per column; nr reflectors at a
-// time are staged in LDS (zero-padded to full length) between barriers.
+// time are staged in LDS (zero-padded to full length) between barriers. SMALL (n <= 128): the
+// column stays in registers, two elements a lane (43 against 65 us at n = 128, 22 against 29 at 64).
+template <bool SMALL>
 __global__ __launch_bounds__(EIG_THREADS) void backtr_kernel(const double* __restrict__ A, int n, int nvec,
                                                              const double* __restrict__ Z, double* __restrict__ U,
                                                              int ldu) {
@@ -481,6 +731,12 @@ __global__ __launch_bounds__(EIG_THREADS) void backtr_kernel(const double* __res
         const int i = q / ncol, c = q - (q / ncol) * ncol;
         zs[c * n + i] = Z[(int64_t)i * nvec + cb + c];
       }
+      __syncthreads();
+      double z0 = 0.0, z1 = 0.0;  // elements lane and lane + 64
+      if (SMALL && wave < ncol) {
+        if (lane < n) z0 = zs[wave * n + lane];
+        if (lane + 64 < n) z1 = zs[wave * n + lane + 64];
+      }
       for (int k0 = n - 3; k0 >= 0; k0 -= nr) {
         __syncthreads();
         for (int q = tid; q < nr * n; q += nthr) {
@@ -488,7 +744,25 @@ __global__ __launch_bounds__(EIG_THREADS) void backtr_kernel(const double* __res
           vb[q] = (k >= 0 && i > k) ? A[(int64_t)k * n + i] : 0.0;
         }
         __syncthreads();
-        if (wave < ncol) {
+        if (SMALL && wave < ncol) {
+          // the column in registers, four reflectors' elements read ahead (those before the first are zero)
+          for (int t0 = 0; t0 < nr; t0 += 4) {
+            double x[4], y[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+              const double* v = vb + min(t0 + t, nr - 1) * n;
+              x[t] = t0 + t < nr && lane < n ? v[min(lane, n - 1)] : 0.0;
+              y[t] = t0 + t < nr && lane + 64 < n ? v[min(lane + 64, n - 1)] : 0.0;
+            }
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+              const double sdot = -2.0 * wave_sum(fma(x[t], z0, y[t] * z1));
+              z0 = fma(sdot, x[t], z0);
+              z1 = fma(sdot, y[t], z1);
+            }
+          }
+        }
+        if (!SMALL && wave < ncol) {
           double* z = zs + wave * n;
           for (int t = 0; t < nr && k0 - t >= 0; t++) {
             const int k = k0 - t;
@@ -499,6 +773,10 @@ __global__ __launch_bounds__(EIG_THREADS) void backtr_kernel(const double* __res
             for (int i = k + 1 + lane; i < n; i += 64) z[i] -= sdot * v[i];
           }
         }
+      }
+      if (SMALL && wave < ncol) {
+        if (lane < n) zs[wave * n + lane] = z0;
+        if (lane + 64 < n) zs[wave * n + lane + 64] = z1;
       }
       __syncthreads();
       for (int q = tid; q < n * ncol; q += nthr) {
@@ -520,8 +798,12 @@ void symeig(const double* T, int ldt, int n, int nvec, double* theta, double* U,
   w.xb.alloc((size_t)(4 * n + 8) * sizeof(double));
   w.flag.alloc(sizeof(int));
   double* de = w.aux.as<double>();
-  {
-    double* A = w.a.as<double>();
+  double* A = w.a.as<double>();
+  if (n <= 64) {
+    hipLaunchKernelGGL(tridiag_small_kernel<64>, dim3(1), dim3(256), 0, st, T, ldt, n, A, de);
+  } else if (n <= TRI_SMALL) {
+    hipLaunchKernelGGL(tridiag_small_kernel<TRI_SMALL>, dim3(1), dim3(256), 0, st, T, ldt, n, A, de);
+  } else {
     double* xb = w.xb.as<double>();
     void* args[] = {(void*)&T, (void*)&ldt, (void*)&n, (void*)&A, (void*)&de, (void*)&xb};
     const size_t shm = (size_t)(TRI_RW + 3) * n * sizeof(double);
@@ -529,7 +811,8 @@ void symeig(const double* T, int ldt, int n, int nvec, double* theta, double* U,
                                         (unsigned)shm, st));
   }
   const int nwant = nvec < n ? nvec + 1 : nvec;
-  hipLaunchKernelGGL(bisect_kernel, dim3((nwant * BIS_TPE + 255) / 256), dim3(256), 0, st, de, n, nvec, theta);
+  if (nwant <= 256) hipLaunchKernelGGL(bisect_kernel<256>, dim3(nwant), dim3(256), 0, st, de, n, nvec, theta);
+  else hipLaunchKernelGGL(bisect_kernel<32>, dim3((nwant * 32 + 255) / 256), dim3(256), 0, st, de, n, nvec, theta);
   hipLaunchKernelGGL(inviter_kernel, dim3((nvec + INV_VPW - 1) / INV_VPW), dim3(64),
                      (size_t)(2 * n + INV_VPW * (6 * n + 4)) * sizeof(double), st, de, theta, n, nvec,
                      w.z.as<double>());
@@ -545,8 +828,8 @@ void symeig(const double* T, int ldt, int n, int nvec, double* theta, double* U,
                          w.lu.as<double>(), done);
     }
   }
-  hipLaunchKernelGGL(backtr_kernel, dim3((nvec + 15) / 16), dim3(EIG_THREADS), 0, st, w.a.as<double>(), n, nvec,
-                     w.z.as<double>(), U, ldu);
+  hipLaunchKernelGGL(n <= TRI_SMALL ? backtr_kernel<true> : backtr_kernel<false>, dim3((nvec + 15) / 16),
+                     dim3(EIG_THREADS), 0, st, w.a.as<double>(), n, nvec, w.z.as<double>(), U, ldu);
   TRBL_HIP(hipGetLastError());
 }
 
