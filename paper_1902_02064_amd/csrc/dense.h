@@ -52,7 +52,9 @@ void t_alpha(double* T, int ldt, int c0, int nb, const double* C1, hipStream_t s
 // C[r, :] = T[r, c0:c0+nb] for r in [r_lo, c0) (C row-major, nb columns)
 void t_column(const double* T, int ldt, int c0, int r_lo, int nb, double* C, hipStream_t st);
 void t_beta(double* T, int ldt, int c0, int m, int nb, const double* beta, hipStream_t st);
-void resid(const double* beta, int nb, const double* U, int ldu, int m, int n, double* rho, hipStream_t st);
+// out (device-visible): rho_i = || beta U[m-nb:m, i] ||, then theta_i, i < n, then theta_{m-1}
+void resid(const double* beta, int nb, const double* U, int ldu, int m, int n, const double* theta, double* out,
+           hipStream_t st);
 void t_restart(double* T, int ldt, int lm, const double* theta, int ls, const double* beta, int nb, const double* U,
                int ldu, int m, hipStream_t st);
 

@@ -719,8 +719,9 @@ __global__ void t_beta_kernel(double* T, int ldt, int c0, int m, int nb, const d
   T[(c0 + j) * ldt + m + i] = beta[i * nb + j];
 }
 
-// residual norms rho_i = || beta U[m-nb:m, i] || for i < n
-__global__ void resid_kernel(const double* beta, int nb, const double* U, int ldu, int m, int n, double* rho) {
+// out: residual norms rho_i = || beta U[m-nb:m, i] || and Ritz values theta_i for i < n, then theta_{m-1}
+__global__ void resid_kernel(const double* beta, int nb, const double* U, int ldu, int m, int n, const double* theta,
+                             double* out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double s = 0.0;
@@ -729,7 +730,9 @@ __global__ void resid_kernel(const double* beta, int nb, const double* U, int ld
     for (int b = 0; b < nb; b++) x += beta[a * nb + b] * U[(m - nb + b) * ldu + i];
     s += x * x;
   }
-  rho[i] = sqrt(s);
+  out[i] = sqrt(s);
+  out[n + i] = theta[i];
+  if (i == 0) out[2 * n] = theta[m - 1];
 }
 
 // restart: T := [diag(theta_1..ls)  r^T ; r  .], r = beta U[m-nb:m, 0:ls] (T zeroed first)
@@ -986,8 +989,9 @@ void t_column(const double* T, int ldt, int c0, int r_lo, int nb, double* C, hip
 void t_beta(double* T, int ldt, int c0, int m, int nb, const double* beta, hipStream_t st) {
   hipLaunchKernelGGL(t_beta_kernel, dim3((nb * nb + 255) / 256), dim3(256), 0, st, T, ldt, c0, m, nb, beta);
 }
-void resid(const double* beta, int nb, const double* U, int ldu, int m, int n, double* rho, hipStream_t st) {
-  hipLaunchKernelGGL(resid_kernel, dim3((n + 255) / 256), dim3(256), 0, st, beta, nb, U, ldu, m, n, rho);
+void resid(const double* beta, int nb, const double* U, int ldu, int m, int n, const double* theta, double* out,
+           hipStream_t st) {
+  hipLaunchKernelGGL(resid_kernel, dim3((n + 255) / 256), dim3(256), 0, st, beta, nb, U, ldu, m, n, theta, out);
 }
 void t_restart(double* T, int ldt, int lm, const double* theta, int ls, const double* beta, int nb, const double* U,
                int ldu, int m, hipStream_t st) {

@@ -71,6 +71,37 @@ struct DevBuf {
   T* as() const { return static_cast<T*>(p); }
 };
 
+// pinned host memory that kernels write to (coherent: visible once the stream has been waited for)
+struct HostBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+  HostBuf() = default;
+  HostBuf(const HostBuf&) = delete;
+  HostBuf& operator=(const HostBuf&) = delete;
+  ~HostBuf() {
+    if (p) (void)hipHostFree(p);
+  }
+  void alloc(size_t n) {
+    if (n <= bytes) return;
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    bytes = 0;
+    if (hipHostMalloc(&p, n, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+      p = nullptr;
+      throw Error{TRBL_E_NOMEM, "pinned host allocation of " + std::to_string(n) + " bytes failed"};
+    }
+    bytes = n;
+  }
+  template <class T>
+  T* host() const { return static_cast<T*>(p); }
+  template <class T>
+  T* dev() const {
+    void* d = nullptr;
+    TRBL_HIP(hipHostGetDevicePointer(&d, p, 0));
+    return static_cast<T*>(d);
+  }
+};
+
 // ---------------------------------------------------------------- model
 struct SpeciesSector {
   int twoM, par;

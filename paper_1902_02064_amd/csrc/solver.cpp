@@ -75,7 +75,7 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
 
   const int64_t ldq = round4(lm);
   const int ldu = std::max(ls, neig);
-  DevBuf Qb, Vkb, Wb, Tb, C1b, C2b, Rb, thb, Ub, rhob, stb;
+  DevBuf Qb, Vkb, Wb, Tb, C1b, C2b, Rb, thb, Ub;
   Qb.alloc((size_t)D * ldq * sizeof(TQ));
   Vkb.alloc((size_t)D * nb * sizeof(TQ));
   // FP64: the new block W is an FP64 work array. Mixed precision: H V_k lands in the basis
@@ -93,8 +93,13 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
   Rb.alloc((size_t)5 * nb * nb * sizeof(double));
   thb.alloc((size_t)lm * sizeof(double));
   Ub.alloc((size_t)lm * ldu * sizeof(double));
-  rhob.alloc((size_t)std::max(neig, 64) * sizeof(double));
-  stb.alloc(4 * sizeof(int));
+  // What the host reads each iteration is written by the kernels straight into pinned host memory: the
+  // Cholesky status of the two QR passes, then residual norms, Ritz values and the largest of them.
+  HostBuf rep;
+  rep.alloc(sizeof(double) * (size_t)(2 + 2 * EIG_NMAX));
+  volatile int* const sth = rep.host<int>();
+  const double* const repv = rep.host<double>() + 1;  // rho[0:n], theta[0:n], max theta
+  double* const repd = rep.dev<double>() + 1;
   TQ* Q = Qb.as<TQ>();
   TQ* Vk = Vkb.as<TQ>();  // packed copy of the current block: H.V stages whole source rows
   double* W = Wb.as<double>();  // FP64 only (mixed: w64() on demand)
@@ -108,8 +113,7 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
   double* beta = R2i + nb * nb;
   double* theta = thb.as<double>();
   double* U = Ub.as<double>();
-  double* rho = rhob.as<double>();
-  int* status = stb.as<int>();
+  int* status = rep.dev<int>();
   Scratch sc;
   EigWork ew;
   Events ev;
@@ -204,8 +208,6 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
     apply_small<double, TQ>(W, nb, R2i, Q, ldq, nb, D, false, sc, st);
   }
   TRBL_HIP(hipMemsetAsync(T, 0, sizeof(double) * (size_t)lm * lm, st));
-  int sth[4] = {0, 0, 0, 0};
-  TRBL_HIP(hipMemcpyAsync(sth, status, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
   TRBL_HIP(hipStreamSynchronize(st));
   if (sth[0] || sth[1]) {  // rank-deficient start block: column-wise QR with replacement
     W = w64();
@@ -283,7 +285,21 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
       apply_small<double, TQ>(W, nb, R2i, Q + mcur, ldq, nb, D, false, sc, st, Vk, nb);
     }
     t_beta(T, lm, c0, mcur, nb, beta, st);
-    TRBL_HIP(hipMemcpyAsync(sth, status, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+    TRBL_HIP(hipEventRecord(ev.e[3], st));
+    // diagonalise T^(k) (every check_every iterations and before every restart); queued behind the QR, so
+    // that the host waits once for both (a breakdown repeats it)
+    const bool restart_next = mcur + 2 * nb > lm;
+    const bool check_now = o.check_every < 0 ? it >= next_check : it % std::max(1, o.check_every) == 0;
+    const bool test = restart_next || check_now || it >= o.max_iter;
+    auto eigen = [&]() {
+      const int nvec = restart_next ? ls : std::min(neig, mcur);
+      symeig(T, lm, mcur, nvec, theta, U, ldu, ew, restart_next, st);  // orthonormal U only where kept
+      last_orth = restart_next;
+      nchk = std::min(neig, mcur);
+      resid(beta, nb, U, ldu, mcur, nchk, theta, repd, st);
+      TRBL_HIP(hipEventRecord(ev.e[4], st));
+    };
+    if (test) eigen();
     TRBL_HIP(hipStreamSynchronize(st));
     if (sth[0] || sth[1]) {
       // breakdown: W was scaled in place; form it again (same arithmetic) and take the
@@ -305,32 +321,21 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
       }
       robust_qr(W, mcur, (uint64_t)it);
       t_beta(T, lm, c0, mcur, nb, beta, st);
-      sth[0] = sth[1] = 0;
+      TRBL_HIP(hipEventRecord(ev.e[3], st));
+      if (test) eigen();
+      TRBL_HIP(hipStreamSynchronize(st));
     } else {
       vk_current = true;
     }
-    TRBL_HIP(hipEventRecord(ev.e[3], st));
-    // diagonalise T^(k) (every check_every iterations and before every restart)
-    const bool restart_next = mcur + 2 * nb > lm;
-    const bool check_now = o.check_every < 0 ? it >= next_check : it % std::max(1, o.check_every) == 0;
-    if (!restart_next && !check_now && it < o.max_iter) {
-      TRBL_HIP(hipEventSynchronize(ev.e[3]));
+    if (!test) {
       t_hv += ev.ms(0, 1);
       t_orth += ev.ms(1, 2);
       t_qr += ev.ms(2, 3);
       continue;
     }
-    const int nvec = restart_next ? ls : std::min(neig, mcur);
-    symeig(T, lm, mcur, nvec, theta, U, ldu, ew, restart_next, st);  // orthonormal U only where kept
-    last_orth = restart_next;
-    nchk = std::min(neig, mcur);
-    resid(beta, nb, U, ldu, mcur, nchk, rho, st);
-    TRBL_HIP(hipEventRecord(ev.e[4], st));
-    TRBL_HIP(hipMemcpyAsync(th.data(), theta, nchk * sizeof(double), hipMemcpyDeviceToHost, st));
-    double tmax = 0.0;
-    TRBL_HIP(hipMemcpyAsync(&tmax, theta + mcur - 1, sizeof(double), hipMemcpyDeviceToHost, st));
-    TRBL_HIP(hipMemcpyAsync(rh.data(), rho, nchk * sizeof(double), hipMemcpyDeviceToHost, st));
-    TRBL_HIP(hipStreamSynchronize(st));
+    std::copy(repv, repv + nchk, rh.begin());
+    std::copy(repv + nchk, repv + 2 * nchk, th.begin());
+    const double tmax = repv[2 * nchk];
     t_hv += ev.ms(0, 1);
     t_orth += ev.ms(1, 2);
     t_qr += ev.ms(2, 3);
