@@ -211,9 +211,12 @@ static void run_fly(const Model& m, int nb, const void* V, int64_t ldv, void* W,
   FlyArgs<T> a{};
   const int64_t D = m.dim;
   const DeviceTables& d = m.dt;
-  // internal-order copies of V and W, kept with the model for the next product
+  // the two-body part by pair blocks; products restricted to a truncated space keep the per-element kernel,
+  // which does not generate the rows outside it
+  const bool tiles = m.flyt.on && !mask;
+  // internal-order copies of V and (per-element kernel) W, kept with the model for the next product
   DevBuf& buf = m.fly_buf[sizeof(T) == 8 ? 1 : 0];
-  buf.alloc((size_t)2 * D * nb * sizeof(T));
+  buf.alloc((size_t)(tiles ? 1 : 2) * D * nb * sizeof(T));
   T* vin = buf.as<T>();
   T* win = vin + D * nb;
   const int nsec = (int)m.sp[m.fly_s].sectors.size();
@@ -245,11 +248,11 @@ static void run_fly(const Model& m, int nb, const void* V, int64_t ldv, void* W,
     a.h = d.fly_h32.as<T>();
     a.e = d.fly_e32.as<T>();
   }
-  // the two-body part by pair blocks (the diagonal in its final pass); products restricted to a
-  // truncated space keep the per-element kernel, which does not generate the rows outside it
-  if (m.flyt.on && !mask) {
-    launch_fly_tiles<T>(m, nb, vin, win, mask, s);
-  } else if (nb <= 8) {
+  if (tiles) {
+    launch_fly_tiles<T>(m, nb, vin, static_cast<T*>(W), ldw, s);
+    return;
+  }
+  if (nb <= 8) {
     const dim3 grid((unsigned)((D + 255) / 256), 1);
     hipLaunchKernelGGL((fly_kernel<T, 8>), grid, dim3(256), 0, s, a);
   } else {

@@ -12,6 +12,12 @@ using namespace tiles;
 
 namespace {
 
+// 4-pair steps of the kernel instance for a block of d pairs
+__host__ __device__ inline int fly_steps(int d) {
+  const int k = (d + 3) / 4;
+  return k <= 6 ? k : k <= 12 ? (k + 1) / 2 * 2 : 16;
+}
+
 // ------------------------------------------------------------------ one species: pairs of identical nucleons
 // A two-body term c+_a c+_b c_d c_c (a < b, c < d) of one species leaves n - 2 nucleons in place,
 // a core L. With the pairs (a, b) of one (2M, parity) listed once, the terms acting on the
@@ -20,12 +26,17 @@ namespace {
 // act on L in the order c, d, then b, a, and a < b, c < d), a target and a source factor. Every
 // term application belongs to exactly one core (the target minus a and b), so the two-body part
 // of W is the sum over the C(n, 2) cores of a target, slot (position of a, position of b) each.
+//
+// A block is the same for every core, so the 16 columns of a matrix instruction are shared by several
+// cores; the pairs that a core blocks read zeros and write nothing.
 template <class T>
 struct FlyTileArgs {
   const T* V;  // internal order, packed nb
   T* Z;
-  int c0, cval, zw;  // column tile: first column, valid columns, slot row width
-  int ns, half, D, vrow;
+  // column tile: first column, valid columns, lanes of a row (a power of two)
+  int c0, cval, lr;
+  int half, D, vrow;
+  unsigned vbytes;
   const uint64_t* cw;  // cores, grouped
   const int* base;     // two-level ranking (sector-major low-part offsets, high-part ranks)
   const int* rank;
@@ -39,229 +50,268 @@ struct FlyTileArgs {
   int nitems;
 };
 
-template <class T, int DTM>
-__device__ __forceinline__ void fly_store(const unsigned* Rt, const int* Pi, int d, int DT, int c, int kq, bool cok,
-                                          T* Z, int64_t D, int zw, const typename Mfma<T>::acc (&acc)[DTM]) {
-#pragma unroll
-  for (int mt = 0; mt < DTM; mt++) {
-    if (mt < DT) {
-#pragma unroll
-      for (int v = 0; v < 4; v++) {
-        const int i = 16 * mt + Mfma<T>::row(kq, v);
-        const unsigned t = Rt[i];
-        const int p = Pi[i];
-        if (i < d && cok)
-          __builtin_nontemporal_store(flip_if((T)acc[mt][v], (unsigned)(p >> 8) & 1u),
-                                      Z + ((int64_t)(p >> 9) * D + t) * zw + c);
-      }
-    }
-  }
-}
+#if defined(__HIP_DEVICE_COMPILE__)  // buffer descriptors exist only in the device pass
+// The cores of one item for a block of at most 4 KS pairs. Lane c of the 16 columns serves core c / lr of
+// KN and VPL adjacent columns (one load or store of up to 16 bytes); VPL instructions take a lane's columns
+// one after the other. A wavefront lists KN cores at a time, a lane per pair (V offset, halved, with the
+// sign of pair and core on top, NO_ROW where the core blocks the pair; slot row), with the rank-table
+// lookups of the next KN issued ahead, runs the KS steps of each 16-target tile over the block's fragments,
+// and during the last tile gathers the source rows of the next KN cores into the registers it has just used.
+template <class T, int VPL, int KN, int KS>
+struct FlyCores {
+  static constexpr int LP = KS <= 4 ? 16 : KS <= 8 ? 32 : 64, PPO = 64 / LP;  // lanes of a core's list
+  static constexpr int NO = KN > PPO ? KN / PPO : 1, DT = (KS + 3) / 4;
+  static constexpr int LW = NO * 64;  // words of one list
+  typedef typename Cols<T, VPL>::type cols;
+  typedef Buf<(int)sizeof(cols)> B;
+  const FlyTileArgs<T>& a;
+  const T* Af;
+  unsigned* L;  // this wavefront's lists: [stage][V offsets, slot rows][LW]
+  const uint64_t* Lc;
+  int count, l, kq, sa, sb, st;
+  const int* bk;
+  bool have;
+  unsigned vh, cb, sbyte, rowb, at0;
+  uint64_t pair, lmask;
+  __amdgpu_buffer_rsrc_t vs;
+  int eb[NO], er[NO];
 
-template <class T, int DTM>
-__device__ __forceinline__ void fly_product(const T* Hs, const unsigned* Rv, const unsigned* Rt, const int* Pi, int d,
-                                            int HW, int c, int kq, bool cok, unsigned cb, const char* Vb, T* Z,
-                                            int64_t D, int zw) {
-  const int KS = (d + 3) >> 2, DT = (d + 15) >> 4;
-  int tb[DTM];
-  typename Mfma<T>::acc acc[DTM];
-#pragma unroll
-  for (int mt = 0; mt < DTM; mt++) {
-    tb[mt] = (Pi[16 * mt + c] & 255) * HW;
-    acc[mt] = typename Mfma<T>::acc{0, 0, 0, 0};
+  __device__ __forceinline__ FlyCores(const FlyTileArgs<T>& a_, const int* Ps, int D2, int sk, const T* Af_,
+                                      unsigned* L_, const uint64_t* Lc_, int count_)
+      : a(a_), Af(Af_), L(L_), Lc(Lc_), count(count_) {
+    l = threadIdx.x & 63;
+    kq = l >> 4;
+    const int c = l & 15, ab = Ps[min(l % LP, D2 - 1)];
+    have = l % LP < D2;
+    sa = ab & 255;
+    sb = ab >> 8;  // sa < sb
+    pair = (1ull << sa) | (1ull << sb);
+    lmask = (1ull << a.half) - 1;
+    st = a.sstart[sk];
+    bk = a.base + ((int64_t)sk << a.half);
+    vh = (unsigned)a.vrow >> 1;
+    rowb = (unsigned)(a.lr * VPL * (int)sizeof(T));
+    const int q = min(c / a.lr, KN - 1);  // lanes beyond KN * lr repeat the last core
+    // columns of this lane: the last one of a ragged row overlaps its neighbour (the same values at the same
+    // place), and lanes beyond it repeat those columns and fill the slot row up
+    const int c1 = VPL * (c % a.lr), c2 = max(min(c1, a.cval - VPL), 0);
+    cb = (unsigned)c2 * (unsigned)sizeof(T);
+    sbyte = (unsigned)(c1 < a.cval ? c2 : c1) * (unsigned)sizeof(T);
+    at0 = (unsigned)(q * LP + kq);
+    vs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.V + a.c0), (short)0, (int)a.vbytes, 0x00020000);
   }
+  __device__ __forceinline__ uint64_t core(int n, int o) const {
+    const int j = n + o * PPO + l / LP;
+    return j < count && o * PPO + l / LP < KN ? Lc[j] : ~0ull;
+  }
+  __device__ __forceinline__ bool free_pair(uint64_t K) const { return have && (K & pair) == 0; }
+  // rank-table lookups of the KN cores from n on
+  __device__ __forceinline__ void entries(int n) {
 #pragma unroll
-  for (int h = 0; h < DTM / 2; h++) {
-    T bop[8];
-    tile_loads<T>(Rv, h, kq, cb, Vb, bop);
+    for (int o = 0; o < NO; o++) {
+      const uint64_t K = core(n, o), x = free_pair(K) ? K | pair : 0ull;
+      eb[o] = bk[x & lmask];
+      er[o] = a.rank[x >> a.half];
+    }
+  }
+  // lists the KN cores from n on, whose lookups are held, then issues those of the cores from `next` on
+  __device__ __forceinline__ void list(int buf, int n, int next) {
+    unsigned* const Rv = L + buf * 2 * LW;
 #pragma unroll
-    for (int j = 0; j < 8; j++) {
-      if (8 * h + j < KS) {
-        const int kk = 4 * (8 * h + j) + kq;
-        const T b = flip_if(bop[j], Rv[kk] & 1u);
-        const int pk = Pi[kk] & 255;
-        T av[DTM];
+    for (int o = 0; o < NO; o++) {
+      const uint64_t K = core(n, o);
+      const unsigned t = (unsigned)(st + eb[o] + er[o]);
+      const int pa = __popcll(K & ((1ull << sa) - 1)), pb = __popcll(K & ((1ull << sb) - 1)) + 1;
+      const unsigned sg = (unsigned)(pa + pb + 1) << 31;  // sigma(K, a) sigma(K, b)
+      Rv[o * 64 + l] = free_pair(K) ? __umul24(t, vh) | sg : NO_ROW >> 1;
+      Rv[LW + o * 64 + l] = __umul24((unsigned)(pb * (pb - 1) / 2 + pa), (unsigned)a.D) + t;
+    }
+    entries(next);
+    // the lists are written and read by this wavefront only: LDS operations of one wavefront
+    // complete in order, so only the compiler must keep them in place
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ __forceinline__ cols gather(const unsigned* Rv, int j) {
+    return __builtin_bit_cast(cols, B::load(vs, (Rv[at0 + 4 * j] << 1) + cb));
+  }
+  static __device__ __forceinline__ T value(const cols& x, int t) {
+    if constexpr (VPL == 1) return x;
+    else return x[t];
+  }
+  static __device__ __forceinline__ cols flipped(cols x, unsigned o) {
+    if constexpr (VPL == 1) {
+      return flip_if(x, o >> 31);
+    } else {
 #pragma unroll
-        for (int mt = 0; mt < DTM; mt++) av[mt] = Hs[tb[mt] + pk];
+      for (int t = 0; t < VPL; t++) x[t] = flip_if((T)x[t], o >> 31);
+      return x;
+    }
+  }
+  __device__ __forceinline__ void run() {
+    int n = (int)(threadIdx.x >> 6) * KN;
+    if (n >= count) return;
+    cols b[KS];
+    entries(n);
+    list(0, n, n + 4 * KN);
 #pragma unroll
-        for (int mt = 0; mt < DTM; mt++)
-          if (mt < DT) acc[mt] = Mfma<T>::run(av[mt], b, acc[mt]);
+    for (int j = 0; j < KS; j++) b[j] = gather(L, j);
+    char* const Zb = reinterpret_cast<char*>(a.Z) + sbyte;
+    int buf = 0;
+    for (; n < count; n += 4 * KN) {
+      const unsigned* const Rv = L + buf * 2 * LW;
+      buf ^= 1;
+      list(buf, n + 4 * KN, n + 8 * KN);  // beyond the last core: no rows
+      const unsigned* const Nv = L + buf * 2 * LW;
+#pragma unroll
+      for (int mt = 0; mt < DT; mt++) {
+        typename Mfma<T>::acc acc[VPL];
+#pragma unroll
+        for (int t = 0; t < VPL; t++) acc[t] = typename Mfma<T>::acc{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < KS; j++) {
+          if (mt == 0) b[j] = flipped(b[j], Rv[at0 + 4 * j]);
+          const T av = Af[(mt * KS + j) * 64 + l];
+#pragma unroll
+          for (int t = 0; t < VPL; t++) acc[t] = Mfma<T>::run(av, value(b[j], t), acc[t]);
+          if (mt == DT - 1) b[j] = gather(Nv, j);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          const int i = at0 - kq + 16 * mt + Mfma<T>::row(kq, v);
+          if (sizeof(T) == 8 && 4 * mt + v >= KS) continue;  // beyond the block in every lane
+          const unsigned o = Rv[i], z = Rv[LW + i];
+          cols x;
+          if constexpr (VPL == 1) {
+            x = (T)acc[0][v];
+          } else {
+#pragma unroll
+            for (int t = 0; t < VPL; t++) x[t] = (T)acc[t][v];
+          }
+          if (o != NO_ROW >> 1) {
+            cols* p = reinterpret_cast<cols*>(Zb + (uint64_t)z * rowb);
+            if constexpr (VPL > 1 && KN <= 4) __builtin_nontemporal_store(flipped(x, o), p);
+            else *p = flipped(x, o);
+          }
+        }
       }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_sched_barrier(0);
   }
-  fly_store<T, DTM>(Rt, Pi, d, DT, c, kq, cok, Z, D, zw, acc);
-}
+};
+#endif
 
-// Four cores of at most 16 allowed pairs each (one row tile, four steps): the 16 source loads of
-// the four are issued together, then the products and stores core by core.
-template <class T>
-__device__ __forceinline__ void fly_batch4(const T* Hs, const unsigned (*Rv)[64], const unsigned (*Rt)[64],
-                                           const int (*Pi)[64], const int (&d)[4], int HW, int c, int kq, bool cok,
-                                           unsigned cb, const char* Vb, T* Z, int64_t D, int zw) {
-  T b[4][4];
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    // a core without allowed pairs has written no list this batch: no loads for it
-    if (d[q] == 0) continue;  // uniform
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const unsigned o = Rv[q][4 * j + kq];
-      b[q][j] = *reinterpret_cast<const T*>(Vb + ((o & ~1u) + cb));
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    if (d[q] == 0) continue;  // uniform
-    const int KS = (d[q] + 3) >> 2;
-    const int tb = (Pi[q][c] & 255) * HW;
-    typename Mfma<T>::acc acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      if (j < KS) {
-        const int kk = 4 * j + kq;
-        acc = Mfma<T>::run(Hs[tb + (Pi[q][kk] & 255)], flip_if(b[q][j], Rv[q][kk] & 1u), acc);
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; v++) {
-      const int i = Mfma<T>::row(kq, v);
-      const unsigned t = Rt[q][i];
-      const int p = Pi[q][i];
-      if (i < d[q] && cok)
-        __builtin_nontemporal_store(flip_if((T)acc[v], (unsigned)(p >> 8) & 1u), Z + ((int64_t)(p >> 9) * D + t) * zw + c);
-    }
-  }
-}
-
-// One work item: up to PN_TPB cores of one (2M, parity) group and one pair block (cores staged in
-// LDS); each wavefront takes every fourth core, four at a time, with the rank-table lookups of its
-// next four issued one batch ahead. Lists per core: V byte offset | source sign, target index,
-// pair index | sign << 8 | slot << 9; padded to 64 entries with a valid row and the zero pair.
-template <class T>
-__global__ __launch_bounds__(256, 4) void fly_tile_kernel(FlyTileArgs<T> a) {
-  extern __shared__ __align__(16) char hs_[];
-  T* Hs = reinterpret_cast<T*>(hs_);
-  __shared__ int Ps[PN_MAXPAIR];
+// One work item: up to PN_TPB cores of one (2M, parity) group and one pair block, which is laid out as the
+// matrix instructions read it (one conflict-free LDS read per fragment). Blocks of up to 16, 32 and 64
+// pairs are launches of their own: registers and LDS of the narrow ones allow 8, 5 and 4 workgroups a CU.
+// 112Sn-like space (D = 6,210,638, 53.8 M cores of 7.5 allowed pairs on average; ms per product): 8 columns
+// FP64 38.0 -> 21.1, 1 column 32.4 -> 8.8, 16 columns 82.0 -> 44.0, 16 columns FP32 64.4 -> 21.7. (Before,
+// each core compacted its allowed pairs: 114 instructions a core and block elements gathered from LDS; in
+// one launch 25.7.) At 8 columns FP64 the slots are 26 GB written and read back; the matrix cores are busy
+// 40 % and the vector units 20 % of the kernel, the rest waits for rows.
+template <class T, int VPL, int KN, int LP>
+__global__ __launch_bounds__(256, LP == 16 ? 8 : LP == 32 ? 5 : 4) void fly_tile_kernel(FlyTileArgs<T> a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __align__(16) char hs_[];  // fragments of the widest block
+  T* Af = reinterpret_cast<T*>(hs_);
+  __shared__ int Ps[LP];
   __shared__ uint64_t Lc[PN_TPB];
-  __shared__ unsigned Rv[4][4][64];
-  __shared__ unsigned Rt[4][4][64];
-  __shared__ int Pi[4][4][64];
+  constexpr int LW = 4 * std::max(KN * LP, 64);  // words of one wavefront's lists
+  __shared__ unsigned L[4 * LW];
   const int item = pn_xcd_item(blockIdx.x, a.nitems);
   if (item >= a.nitems) return;
   const int4 it = a.items[item];
   const int k = a.rect[2 * it.x], sk = a.rect[2 * it.x + 1];
-  const int q0 = a.pr_off[k], D2 = a.pr_off[k + 1] - q0, HW = D2 + 1;
+  const int q0 = a.pr_off[k], D2 = a.pr_off[k + 1] - q0;
   const T* hg = a.hb + a.hb_off[k];
-  for (int i = threadIdx.x / 64; i < HW; i += 4)
-    for (int j = threadIdx.x % 64; j < HW; j += 64) Hs[i * HW + j] = (i < D2 && j < D2) ? hg[i * D2 + j] : T(0);
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   for (int e = threadIdx.x; e < D2; e += 256) Ps[e] = a.pr_ab[q0 + e];
   for (int e = threadIdx.x; e < it.z; e += 256) Lc[e] = a.cw[it.y + e];
-  __syncthreads();
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int c = l & 15, kq = l >> 4;
-  const bool cok = c < a.cval;
-  const unsigned cb = (unsigned)(a.c0 + min(c, a.cval - 1)) * (unsigned)sizeof(T);
-  const int lp = min(l, D2 - 1);
-  const int ab = Ps[lp], sa = ab & 255, sb = ab >> 8;  // sa < sb
-  const int st = a.sstart[sk];
-  const int* bk = a.base + ((int64_t)sk << a.half);
-  const uint64_t lmask = (1ull << a.half) - 1, pair = (1ull << sa) | (1ull << sb);
-  const char* Vb = reinterpret_cast<const char*>(a.V);
-  const int n = it.z;
-  // target index of pair l on core j (0 when not allowed), its lookups issued now
-  auto target = [&](int j) __attribute__((always_inline)) {
-    if (j >= n) return 0;
-    const uint64_t L = Lc[j];
-    if (l >= D2 || (L & pair) != 0) return 0;
-    const uint64_t x = L | pair;
-    return st + bk[x & lmask] + a.rank[x >> a.half];
-  };
-  int tn[4];
-#pragma unroll
-  for (int q = 0; q < 4; q++) tn[q] = target(w + 4 * q);
-  for (int j0 = w; j0 < n; j0 += 16) {
-    int tc[4], d[4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) tc[q] = tn[q];
-#pragma unroll
-    for (int q = 0; q < 4; q++) tn[q] = target(j0 + 16 + 4 * q);
-    bool big = false;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int j = j0 + 4 * q;
-      const uint64_t L = j < n ? Lc[j] : ~0ull;
-      const bool ok = l < D2 && (L & pair) == 0;
-      const uint64_t mask = __ballot(ok);
-      d[q] = __popcll(mask);
-      big = big || d[q] > 16;
-      if (d[q] == 0) continue;  // uniform
-      const int below = __popcll(mask & ((1ull << l) - 1));
-      const int t = tc[q];
-      const int lead = __builtin_amdgcn_readlane(t, __builtin_ctzll(mask));
-      if (ok) {
-        const int pa = __popcll(L & ((1ull << sa) - 1)), pb = __popcll(L & ((1ull << sb) - 1)) + 1;
-        const unsigned sg = (unsigned)((pa + pb + 1) & 1);  // sigma(L, a) sigma(L, b)
-        Rv[w][q][below] = (unsigned)t * (unsigned)a.vrow | sg;
-        Rt[w][q][below] = (unsigned)t;
-        Pi[w][q][below] = l | (int)(sg << 8) | ((pb * (pb - 1) / 2 + pa) << 9);
-      } else {
-        const int pad = d[q] + l - below;
-        Rv[w][q][pad] = (unsigned)lead * (unsigned)a.vrow;
-        Pi[w][q][pad] = D2;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (!big) {
-      fly_batch4<T>(Hs, Rv[w], Rt[w], Pi[w], d, HW, c, kq, cok, cb, Vb, a.Z, a.D, a.zw);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; q++) {
-        if (d[q] > 32) fly_product<T, 4>(Hs, Rv[w][q], Rt[w][q], Pi[w][q], d[q], HW, c, kq, cok, cb, Vb, a.Z, a.D, a.zw);
-        else if (d[q] > 0)
-          fly_product<T, 2>(Hs, Rv[w][q], Rt[w][q], Pi[w][q], d[q], HW, c, kq, cok, cb, Vb, a.Z, a.D, a.zw);
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
+  const int KS = fly_steps(D2), nf = (KS + 3) / 4 * KS;
+  for (int f = w; f < nf; f += 4) {
+    const int i = f / KS * 16 + (l & 15), j = f % KS * 4 + (l >> 4);
+    Af[f * 64 + l] = i < D2 && j < D2 ? hg[i * D2 + j] : T(0);
   }
+  __syncthreads();
+#define TRBL_CORES(K) \
+  case K: FlyCores<T, VPL, KN, K>(a, Ps, D2, sk, Af, L + w * LW, Lc, it.z).run(); break
+  if constexpr (LP == 16) {
+    switch (KS) {
+      TRBL_CORES(1);
+      TRBL_CORES(2);
+      TRBL_CORES(3);
+      TRBL_CORES(4);
+    }
+  } else if constexpr (LP == 32) {
+    switch (KS) {
+      TRBL_CORES(5);
+      TRBL_CORES(6);
+      TRBL_CORES(8);
+    }
+  } else {
+    switch (KS) {
+      TRBL_CORES(10);
+      TRBL_CORES(12);
+      TRBL_CORES(16);
+    }
+  }
+#undef TRBL_CORES
+#endif
 }
 
-// W[t][c0 + c] = (single-particle energies of t) V[t][c0 + c] + the slots of t in slot order
-// (internal order, packed nb); targets outside a truncated space (mask 0) get 0
+// W[t][c0 ..] = (single-particle energies of t) V[t][c0 ..] + the slots of t in slot order, 16 bytes of
+// columns a thread (t and V in the internal order, V packed nb, cpr chunks to a slot row; W in Table-1 order)
 template <class T>
-__global__ void fly_finalize_kernel(const T* __restrict__ V, T* __restrict__ W, int nb, const T* __restrict__ Z, int S,
-                                    int64_t D, int zw, int c0, int cval, const uint64_t* words, const T* e,
-                                    const double* mask, const int* perm, const int64_t* soff, const int* sstart,
-                                    int nsec) {
-  const int64_t n = D * zw;
+__global__ void fly_finalize_kernel(const T* __restrict__ V, int nb, T* __restrict__ W, int64_t ldw,
+                                    const T* __restrict__ Z, int S, int64_t D, int cpr, int c0, int cval,
+                                    const uint64_t* words, const T* e, const int* sstart, const int64_t* soff,
+                                    const int* perm, int nsec) {
+  constexpr int VPC = 16 / (int)sizeof(T);
+  typedef T zv __attribute__((ext_vector_type(VPC)));
+  const int64_t n = D * cpr;
   for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(q % zw);
+    const int64_t t = q / cpr;
+    const int c = (int)(q - t * cpr) * VPC;
     if (c >= cval) continue;
-    const int64_t t = q / zw;
-    T* wt = W + t * nb + c0 + c;
-    if (mask) {
-      int k = 0;
-      while (k + 1 < nsec && t >= sstart[k + 1]) k++;
-      if (mask[soff[k] + perm[t]] == 0.0) {
-        *wt = T(0);
-        continue;
-      }
-    }
-    T s = T(0);
-    for (uint64_t x = words[t]; x; x &= x - 1) s += e[__builtin_ctzll(x)];
-    s *= V[t * nb + c0 + c];
-    const T* z = Z + t * zw + c;
+    T d = T(0);
+    for (uint64_t x = words[t]; x; x &= x - 1) d += e[__builtin_ctzll(x)];
+    const T* vt = V + t * nb + c0 + c;
+    zv s;
+#pragma unroll
+    for (int j = 0; j < VPC; j++) s[j] = c + j < cval ? d * vt[j] : T(0);
+    const zv* z = reinterpret_cast<const zv*>(Z) + q;
     int k = 0;
     for (; k + 8 <= S; k += 8) {
-      T zq[8];
+      zv zq[8];
 #pragma unroll
-      for (int j = 0; j < 8; j++) zq[j] = __builtin_nontemporal_load(z + (int64_t)(k + j) * D * zw);
+      for (int j = 0; j < 8; j++) zq[j] = __builtin_nontemporal_load(z + (k + j) * n);
 #pragma unroll
       for (int j = 0; j < 8; j++) s += zq[j];
     }
-    for (; k < S; k++) s += __builtin_nontemporal_load(z + (int64_t)k * D * zw);
-    *wt = s;
+    for (; k < S; k++) s += __builtin_nontemporal_load(z + k * n);
+    int sec = 0;
+    while (sec + 1 < nsec && t >= sstart[sec + 1]) sec++;
+    T* wt = W + (soff[sec] + perm[t]) * ldw + c0 + c;
+#pragma unroll
+    for (int j = 0; j < VPC; j++)
+      if (c + j < cval) wt[j] = s[j];
   }
+}
+
+template <class T, int VPL, int KN, int LP>
+void launch_class(FlyTileArgs<T> a, const int4* items, const int* first, int max_pairs, hipStream_t s) {
+  const int cl = LP == 16 ? 0 : LP == 32 ? 1 : 2, ks = fly_steps(std::min(LP, max_pairs));
+  a.items = items + first[cl];
+  a.nitems = first[cl + 1] - first[cl];
+  if (a.nitems == 0) return;
+  hipLaunchKernelGGL((fly_tile_kernel<T, VPL, KN, LP>), dim3((unsigned)((a.nitems + 7) / 8 * 8)), dim3(256),
+                     (size_t)((ks + 3) / 4 * ks) * 64 * sizeof(T), s, a);
+}
+template <class T, int VPL, int KN>
+void launch_tile(const FlyTileArgs<T>& a, const FlyTiles& F, hipStream_t s) {
+  const int4* items = F.items_buf.as<int4>();
+  launch_class<T, VPL, KN, 64>(a, items, F.first, F.max_pairs, s);
+  launch_class<T, VPL, KN, 32>(a, items, F.first, F.max_pairs, s);
+  launch_class<T, VPL, KN, 16>(a, items, F.first, F.max_pairs, s);
 }
 
 }  // namespace
@@ -342,7 +392,7 @@ void build_fly_tiles(Model& m) {
     }
   }
   std::vector<uint64_t> cw;
-  std::vector<int> rect, items;
+  std::vector<int> rect, items, cls[3];  // work items by lanes of a core's list: 16, 32, 64
   for (auto& kv : by) {
     std::vector<std::pair<int, int>> rs;  // (pair block, sector)
     for (const auto& sv : secid) {
@@ -363,21 +413,25 @@ void build_fly_tiles(Model& m) {
     for (const auto& r : rs) {
       const int ri = (int)(rect.size() / 2);
       rect.insert(rect.end(), {r.first, r.second});
-      for (int q = 0; q < n; q += PN_TPB) items.insert(items.end(), {ri, c0 + q, std::min(PN_TPB, n - q), 0});
+      const int np = (int)pairs[r.first].size();
+      std::vector<int>& to = cls[np <= 16 ? 0 : np <= 32 ? 1 : 2];
+      for (int q = 0; q < n; q += PN_TPB) to.insert(to.end(), {ri, c0 + q, std::min(PN_TPB, n - q), 0});
     }
+  }
+  for (int q = 0; q < 3; q++) {
+    items.insert(items.end(), cls[q].begin(), cls[q].end());
+    F.first[q + 1] = (int)(items.size() / 4);
   }
   if (items.empty()) return;
   TRBL_REQUIRE(items.size() / 4 < ((size_t)1 << 31) / 256, TRBL_E_INVALID, "too many cores for one launch");
   const int S = npart * (npart - 1) / 2;
-  const int zw = 8;  // slot rows of 8 columns; wider products run in tiles of 8
-  const size_t zbytes = (size_t)S * (size_t)m.dim * zw * sizeof(double);
+  const size_t zbytes = (size_t)S * (size_t)m.dim * 64;  // slot rows of at most 64 bytes
   size_t fr = 0, tot = 0;
   TRBL_HIP(hipMemGetInfo(&fr, &tot));
-  if (zbytes > fr / 4 || (double)m.dim * 64 * 8 >= 4294967296.0 || (double)S * m.dim >= 4294967296.0) return;
+  // (V of 64 columns below NO_ROW bytes)
+  if (zbytes > fr / 4 || (double)m.dim * 64 * 8 > (double)NO_ROW || (double)S * m.dim >= 4294967296.0) return;
   F.S = S;
-  F.zw = zw;
   F.max_pairs = maxp;
-  F.items = (int64_t)(items.size() / 4);
   F.cw.upload(cw);
   F.pr_off.upload(pr_off);
   F.pr_ab.upload(pr_ab);
@@ -391,14 +445,13 @@ void build_fly_tiles(Model& m) {
 }
 
 template <class T>
-void launch_fly_tiles(const Model& m, int nb, const T* Vint, T* Wint, const double* mask, hipStream_t s) {
+void launch_fly_tiles(const Model& m, int nb, const T* Vint, T* W, int64_t ldw, hipStream_t s) {
+  constexpr int VPC = 16 / (int)sizeof(T), WIDE = 64 / (int)sizeof(T);  // values per lane, most columns at once
   const FlyTiles& F = m.flyt;
   const DeviceTables& d = m.dt;
   FlyTileArgs<T> a{};
   a.V = Vint;
   a.Z = F.z.as<T>();
-  a.zw = F.zw;
-  a.ns = m.ns;
   a.half = m.fly_half;
   a.D = (int)m.dim;
   a.vrow = (int)(nb * sizeof(T));
@@ -411,23 +464,27 @@ void launch_fly_tiles(const Model& m, int nb, const T* Vint, T* Wint, const doub
   a.hb_off = F.hb_off.as<int>();
   a.hb = (sizeof(T) == 8 ? F.hb : F.hb32).as<T>();
   a.rect = F.rect.as<int>();
-  a.items = F.items_buf.as<int4>();
-  a.nitems = (int)F.items;
-  const unsigned grid = (unsigned)((F.items + 7) / 8 * 8);
-  const size_t shm = (size_t)(F.max_pairs + 1) * (F.max_pairs + 1) * sizeof(T);
-  const int nsec = (int)m.sp[m.fly_s].sectors.size();
-  for (int c0 = 0; c0 < nb; c0 += F.zw) {
+  for (int c0 = 0; c0 < nb; c0 += WIDE) {
     a.c0 = c0;
-    a.cval = std::min(F.zw, nb - c0);
-    hipLaunchKernelGGL(fly_tile_kernel<T>, dim3(grid), dim3(256), shm, s, a);
-    hipLaunchKernelGGL(fly_finalize_kernel<T>, dim3(elementwise_grid(m.dim * F.zw)), dim3(256), 0, s, Vint, Wint, nb,
-                       (const T*)a.Z, F.S, m.dim, F.zw, c0, a.cval, d.fly_wint.as<uint64_t>(),
-                       (sizeof(T) == 8 ? d.fly_e64 : d.fly_e32).as<T>(), mask, d.fly_perm.as<int>(),
-                       d.fly_soff.as<int64_t>(), d.fly_sstart.as<int>(), nsec);
+    a.cval = std::min(WIDE, nb - c0);
+    a.vbytes = (unsigned)(m.dim * a.vrow - c0 * (int64_t)sizeof(T));
+    const int cpr = pn_slot_stride(sizeof(T), a.cval);  // 16-byte chunks of a slot row
+    if (a.cval < VPC) {
+      a.lr = VPC;  // one value a lane
+      launch_tile<T, 1, 16 / VPC>(a, F, s);
+    } else {
+      a.lr = cpr;
+      if (cpr <= 2) launch_tile<T, VPC, 8>(a, F, s);
+      else launch_tile<T, VPC, 4>(a, F, s);
+    }
+    hipLaunchKernelGGL(fly_finalize_kernel<T>, dim3(elementwise_grid(m.dim * cpr)), dim3(256), 0, s, Vint, nb, W, ldw,
+                       (const T*)a.Z, F.S, m.dim, cpr, c0, a.cval, d.fly_wint.as<uint64_t>(),
+                       (sizeof(T) == 8 ? d.fly_e64 : d.fly_e32).as<T>(), a.sstart, d.fly_soff.as<int64_t>(),
+                       d.fly_perm.as<int>(), (int)m.sp[m.fly_s].sectors.size());
   }
   TRBL_HIP(hipGetLastError());
 }
-template void launch_fly_tiles<double>(const Model&, int, const double*, double*, const double*, hipStream_t);
-template void launch_fly_tiles<float>(const Model&, int, const float*, float*, const double*, hipStream_t);
+template void launch_fly_tiles<double>(const Model&, int, const double*, double*, int64_t, hipStream_t);
+template void launch_fly_tiles<float>(const Model&, int, const float*, float*, int64_t, hipStream_t);
 
 }  // namespace trbl

@@ -221,13 +221,13 @@ struct PNTiles {
 // of n - 2 nucleons, pairs (a < b) by (2M, parity), C(n, 2) slots per state.
 struct FlyTiles {
   bool on = false;
-  int S = 0, zw = 8, max_pairs = 0;
-  int64_t items = 0;
+  int S = 0, max_pairs = 0;
+  int first[4] = {0, 0, 0, 0};       // work items by width of their pair block (up to 16, 32, 64 pairs)
   DevBuf cw;                         // cores, grouped by (2M, parity)
   DevBuf pr_off, pr_ab, hb_off, hb, hb32;
   DevBuf rect;                       // per rectangle: pair block, target sector
   DevBuf items_buf;                  // per work item: rectangle, first core, count, 0
-  DevBuf z;                          // slot buffer [S][D][zw]
+  DevBuf z;                          // slot buffer [S][D], rows of at most 64 bytes
 };
 
 struct MTerm {  // m-scheme two-body term c+_a c+_b c_d c_c (species-local state indices)
@@ -289,9 +289,9 @@ void build_hamiltonian(Model& m, const double* spe_p, const double* spe_n, const
 void build_fly_basis(Model& m);
 void build_fly_terms(Model& m);
 void build_fly_tiles(Model& m);
-// internal-order block product of a single-species space by pair blocks (Vint, Wint packed nb)
+// block product of a single-species space by pair blocks (Vint in the internal order, packed nb)
 template <class T>
-void launch_fly_tiles(const Model& m, int nb, const T* Vint, T* Wint, const double* mask, hipStream_t s);
+void launch_fly_tiles(const Model& m, int nb, const T* Vint, T* W, int64_t ldw, hipStream_t s);
 // mask (optional, Table-1 order): rows with mask 0 are set to zero without being generated
 void launch_fly(const Model& m, int precision, int nb, const void* V, int64_t ldv, void* W, int64_t ldw,
                 hipStream_t s, const double* mask = nullptr);

@@ -120,48 +120,7 @@ struct PairList {
   int u[PN_MAXPAIR], row[PN_MAXPAIR], z[PN_MAXPAIR], pos[PN_MAXPAIR], step[PN_MAXPAIR], id[PN_MAXPAIR];
 };
 
-// A byte offset beyond every V and slot offset: buffer loads return 0 there, stores write nothing.
-constexpr unsigned NO_ROW = 0xFFFF0000u;
-
-// Buffer accesses. Slot rows of 64 bytes or more are streamed past the caches (NT): they are read back by
-// a later kernel; narrower rows are left for the L2 to merge into whole lines.
-#if defined(__HIP_DEVICE_COMPILE__)  // buffer descriptors exist only in the device pass
-template <int BYTES>
-struct Buf;
-template <>
-struct Buf<4> {
-  typedef unsigned raw;
-  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
-    return __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
-  }
-  template <bool NT>
-  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, o, 0, NT ? 2 : 0);
-  }
-};
-template <>
-struct Buf<8> {
-  typedef unsigned raw __attribute__((ext_vector_type(2)));
-  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
-    return __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
-  }
-  template <bool NT>
-  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, o, 0, NT ? 2 : 0);
-  }
-};
-template <>
-struct Buf<16> {
-  typedef unsigned raw __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
-  }
-  template <bool NT>
-  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, o, 0, NT ? 2 : 0);
-  }
-};
-
+#if defined(__HIP_DEVICE_COMPILE__)
 // The core pairs of one item whose proton core allows d <= 4 KS pair states. The block is the same for
 // every neutron core, so the 16 columns of a matrix instruction are shared by KN of them: lane c
 // serves neutron core c / lr and VPL adjacent columns (one load or store of up to 16 bytes), and VPL

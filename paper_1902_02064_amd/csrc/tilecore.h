@@ -1,6 +1,6 @@
 // Shared pieces of the pair-block kernels (pntile.hip: proton-neutron part; flytile.hip:
 // single-species two-body part): the matrix-core instruction per precision and its output layout,
-// the sign flip, the work-item order and the gathers of one group of source rows.
+// the sign flip, the work-item order and the buffer accesses.
 #pragma once
 #include "internal.h"
 
@@ -55,15 +55,48 @@ struct Cols<T, 1> {
   typedef T type;
 };
 
-template <class T>
-__device__ __forceinline__ void tile_loads(const unsigned* Rv, int h, int kq, unsigned cb, const char* Vb,
-                                           T (&bop)[8]) {
-#pragma unroll
-  for (int j = 0; j < 8; j++) {
-    const unsigned o = Rv[4 * (8 * h + j) + kq];
-    bop[j] = *reinterpret_cast<const T*>(Vb + ((o & ~1u) + cb));
+// A byte offset beyond every V and slot offset: buffer loads return 0 there, stores write nothing.
+constexpr unsigned NO_ROW = 0xFFFF0000u;
+
+// Buffer accesses. Slot rows of 64 bytes or more are streamed past the caches (NT): they are read back by
+// a later kernel; narrower rows are left for the L2 to merge into whole lines.
+#if defined(__HIP_DEVICE_COMPILE__)  // buffer descriptors exist only in the device pass
+template <int BYTES>
+struct Buf;
+template <>
+struct Buf<4> {
+  typedef unsigned raw;
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0);
   }
-}
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+template <>
+struct Buf<8> {
+  typedef unsigned raw __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
+  }
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+template <>
+struct Buf<16> {
+  typedef unsigned raw __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ raw load(__amdgpu_buffer_rsrc_t r, unsigned o) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
+  }
+  template <bool NT>
+  static __device__ __forceinline__ void store(raw v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, o, 0, NT ? 2 : 0);
+  }
+};
+#endif
 
 inline int64_t binom(int n, int k) {
   if (k < 0 || k > n) return 0;
@@ -71,7 +104,6 @@ inline int64_t binom(int n, int k) {
   for (int i = 0; i < k; i++) r = r * (n - i) / (i + 1);
   return (int64_t)(r + 0.5L);
 }
-
 
 }  // namespace tiles
 }  // namespace trbl
