@@ -48,9 +48,7 @@ void copy_cols(const TS* src, int64_t lds_, TD* dst, int64_t ldd, int64_t D, int
 // X[r, 0:ncol] = 0 where mask[r] == 0 (no-op for a null mask)
 template <class T>
 void mask_rows(T* X, int64_t ld, int64_t D, int ncol, const double* mask, hipStream_t st);
-void t_alpha(double* T, int ldt, int c0, int nb, const double* C1, hipStream_t st);
-// C[r, :] = T[r, c0:c0+nb] for r in [r_lo, c0) (C row-major, nb columns)
-void t_column(const double* T, int ldt, int c0, int r_lo, int nb, double* C, hipStream_t st);
+void t_alpha(double* T, int ldt, int c0, int r_lo, int nb, double* C, hipStream_t st);
 void t_beta(double* T, int ldt, int c0, int m, int nb, const double* beta, hipStream_t st);
 // out (device-visible): rho_i = || beta U[m-nb:m, i] ||, then theta_i, i < n, then theta_{m-1}
 void resid(const double* beta, int nb, const double* U, int ldu, int m, int n, const double* theta, double* out,

@@ -85,27 +85,34 @@ __global__ __launch_bounds__(256) void tn_partial_kernel(const TA* __restrict__ 
   const int64_t r0 = (int64_t)blockIdx.x * rows_per;
   const int64_t r1 = min(D, r0 + rows_per);
   const int li = lane & 15, lk = lane >> 4;
-  for (int64_t r = r0 + 4 * wave; r < r1; r += 4 * WAVES) {
-    const int64_t rr = r + lk;
-    const bool rok = rr < r1;
-    double bop[MAXC];
+  constexpr int U = MAXC == 1 ? 2 : 1;  // row quads whose loads are issued together
+  for (int64_t r = r0 + 4 * wave; r < r1; r += 4 * WAVES * U) {
+    double bop[U][MAXC], a4[U][NP][4];
 #pragma unroll
-    for (int q = 0; q < MAXC; q++) {
-      const int c = q * 16 + li;
-      bop[q] = (q < ct && rok && c < nb) ? ld(B + rr * ldb + c) : 0.0;
+    for (int u = 0; u < U; u++) {
+      const int64_t rr = r + 4 * WAVES * u + lk;
+      const bool rok = rr < r1;
+#pragma unroll
+      for (int q = 0; q < MAXC; q++) {
+        const int c = q * 16 + li;
+        bop[u][q] = (q < ct && rok && c < nb) ? ld(B + rr * ldb + c) : 0.0;
+      }
+#pragma unroll
+      for (int p = 0; p < NP; p++) {
+        const int c0 = cbase + 64 * p + 4 * li;
+        if (rok && c0 < m) ld4(A + rr * lda + c0, m - c0, a4[u][p]);
+        else a4[u][p][0] = a4[u][p][1] = a4[u][p][2] = a4[u][p][3] = 0.0;
+      }
     }
 #pragma unroll
-    for (int p = 0; p < NP; p++) {
-      const int c0 = cbase + 64 * p + 4 * li;
-      double a4[4];
-      if (rok && c0 < m) ld4(A + rr * lda + c0, m - c0, a4);
-      else a4[0] = a4[1] = a4[2] = a4[3] = 0.0;
+    for (int u = 0; u < U; u++)
 #pragma unroll
-      for (int t = 0; t < 4; t++)
+      for (int p = 0; p < NP; p++)
 #pragma unroll
-        for (int q = 0; q < MAXC; q++)
-          if (q < ct) acc[p][t][q] = mfma(a4[t], bop[q], acc[p][t][q]);
-    }
+        for (int t = 0; t < 4; t++)
+#pragma unroll
+          for (int q = 0; q < MAXC; q++)
+            if (q < ct) acc[p][t][q] = mfma(a4[u][p][t], bop[u][q], acc[p][t][q]);
   }
   // combine the waves' sums in LDS (one wave after the other), then write the chunk's partial
   constexpr int NBS = 16 * MAXC;
@@ -134,24 +141,38 @@ __global__ __launch_bounds__(256) void tn_partial_kernel(const TA* __restrict__ 
   for (int e = threadIdx.x; e < ncol * nb; e += blockDim.x) out[e] = red[(e / nb) * NBS + e % nb];
 }
 
-// out[k] = sum_g part[g * len + k]: 16 outputs per block, 16 threads share the G terms of each
-// (fixed summation order, so results are reproducible)
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __restrict__ part, int G, int64_t len,
-                                                              double* __restrict__ out) {
-  __shared__ double red[16][17];
+// out[k] = sum_g part[g * len + k]: 16 outputs per block, NG threads share the G terms of each
+// (fixed summation order, so results are reproducible). The loads of a thread are its whole time.
+template <int NG>
+__global__ __launch_bounds__(16 * NG) void reduce_partials_kernel(const double* __restrict__ part, int G, int64_t len,
+                                                                  double* __restrict__ out) {
+  __shared__ double red[NG][17];
   const int kx = threadIdx.x & 15, gy = threadIdx.x >> 4;
   const int64_t k = (int64_t)blockIdx.x * 16 + kx;
   double s = 0.0;
   if (k < len)
 #pragma unroll 8
-    for (int g = gy; g < G; g += 16) s += part[(int64_t)g * len + k];
+    for (int g = gy; g < G; g += NG) s += part[(int64_t)g * len + k];
   red[gy][kx] = s;
   __syncthreads();
+  if (NG > 16) {
+    if (gy < 16) {
+      for (int j = gy + 16; j < NG; j += 16) s += red[j][kx];
+      red[gy][kx] = s;
+    }
+    __syncthreads();
+  }
   if (gy == 0 && k < len) {
     double t = 0.0;
+#pragma unroll
     for (int j = 0; j < 16; j++) t += red[j][kx];
     out[k] = t;
   }
+}
+static void reduce_partials(const double* part, int G, int64_t len, double* out, hipStream_t st) {
+  const dim3 grid((unsigned)((len + 15) / 16));
+  if (G > 64) hipLaunchKernelGGL(reduce_partials_kernel<64>, grid, dim3(1024), 0, st, part, G, len, out);
+  else hipLaunchKernelGGL(reduce_partials_kernel<16>, grid, dim3(256), 0, st, part, G, len, out);
 }
 
 // ------------------------------------------------------------------ Bout = Bin - A C (+ fused partial product)
@@ -489,6 +510,73 @@ __global__ __launch_bounds__(256) void apply_small_kernel(const TI* Bin, int64_t
   }
 }
 
+// The same as chol_kernel below for nb <= 16, one element (i, j) of the matrix a thread, and for nb <= 8 with
+// the sum of the partials in the same launch, 16 or 64 threads an element. A step of the elimination (kept as
+// a_ij - a_ki a_kj / a_kk, the roots taken at the end) costs one barrier, against three in LDS. nb = 8, 256
+// partials: 10 us, 13 us as a sum and a factorisation in LDS.
+__global__ __launch_bounds__(1024) void chol_small_kernel(const double* __restrict__ part, int G, int nb, double* R,
+                                                          double* Rinv, const double* Rprev, double* beta,
+                                                          int* status) {
+  __shared__ double sum[1024], row[2][16], A[16 * 17], Ri[16 * 17], rd[16], diag[16];
+  __shared__ int bad;
+  const int tid = threadIdx.x, n2 = nb * nb;
+  const int len = n2 <= 16 ? 16 : n2 <= 64 ? 64 : 256, ng = 1024 / len;
+  const int e = tid % len, g0 = tid / len;
+  const int i = e / nb, j = e % nb;
+  const bool mine = tid < n2;
+  double s = 0.0;
+  if (e < n2) {
+#pragma unroll 8
+    for (int g = g0; g < G; g += ng) s += part[(int64_t)g * n2 + e];
+  }
+  sum[tid] = s;
+  if (tid == 0) bad = 0;
+  __syncthreads();
+  if (mine) {
+    for (int g = 1; g < ng; g++) s += sum[g * len + e];
+    if (i == j) diag[i] = fabs(s);
+  }
+  __syncthreads();
+  double dmax = 0.0;
+  for (int q = 0; q < nb; q++) dmax = fmax(dmax, diag[q]);
+  for (int k = 0; k < nb; k++) {
+    if (mine && i == k) row[k & 1][j] = s;
+    __syncthreads();
+    const double piv = row[k & 1][k];
+    // beyond a condition number of ~1e7 Cholesky QR loses accuracy: take the column-wise path
+    if (tid == 0 && (!(piv > 1e-14 * dmax) || !(dmax > 0.0))) bad = 1;
+    const double p = fmax(piv, 1e-300);
+    if (mine && i == k) {
+      if (j == k) rd[k] = 1.0 / sqrt(p);
+      A[k * 17 + j] = j < k ? 0.0 : j == k ? sqrt(p) : s / sqrt(p);
+    }
+    if (mine && i > k && j >= i) s -= row[k & 1][i] * row[k & 1][j] / p;
+  }
+  __syncthreads();
+  // inverse of the upper-triangular R, one thread per column
+  if (tid < nb) {
+    const int c = tid;
+    for (int q = nb - 1; q > c; q--) Ri[q * 17 + c] = 0.0;
+    Ri[c * 17 + c] = rd[c];
+    for (int q = c - 1; q >= 0; q--) {
+      double t = 0.0;
+      for (int k = q + 1; k <= c; k++) t += A[q * 17 + k] * Ri[k * 17 + c];
+      Ri[q * 17 + c] = -t * rd[q];
+    }
+  }
+  __syncthreads();
+  if (mine) {
+    R[e] = A[i * 17 + j];
+    Rinv[e] = Ri[i * 17 + j];
+    if (beta) {
+      double t = 0.0;
+      for (int k = 0; k < nb; k++) t += A[i * 17 + k] * Rprev[k * nb + j];
+      beta[e] = t;
+    }
+  }
+  if (tid == 0) status[0] = bad;
+}
+
 // ------------------------------------------------------------------ Cholesky of the nb x nb Gram matrix
 // Sums G partials, factors G = R^T R (R upper, positive diagonal), inverts R,
 // and optionally forms beta = R * Rprev. status[0] = 0 ok, 1 not positive definite.
@@ -695,20 +783,13 @@ __global__ void copy_cols_kernel(const TS* src, int64_t lds_, TD* dst, int64_t l
 }
 
 // T-matrix bookkeeping of Alg. 4 (device-resident T, leading dimension ldt)
-__global__ void t_alpha_kernel(double* T, int ldt, int c0, int nb, const double* C1) {
-  // alpha_k = V_k^T W is rows c0..c0+nb of C1 (m x nb); symmetrised
+// alpha_k = V_k^T W, rows c0.. of C (m x nb), symmetrised into T; rows r_lo..c0-1 of C := T's column block c0
+// (the couplings of V_k to the earlier vectors)
+__global__ void t_alpha_kernel(double* T, int ldt, int c0, int r_lo, int nb, double* C) {
   const int e = threadIdx.x + blockIdx.x * blockDim.x;
-  if (e >= nb * nb) return;
   const int i = e / nb, j = e % nb;
-  T[(c0 + i) * ldt + c0 + j] = 0.5 * (C1[(c0 + i) * nb + j] + C1[(c0 + j) * nb + i]);
-}
-
-__global__ void t_column_kernel(const double* T, int ldt, int c0, int r_lo, int nb, double* C) {
-  // rows r_lo..c0-1 of column block c0 of T (the couplings of V_k to the earlier vectors)
-  const int e = threadIdx.x + blockIdx.x * blockDim.x;
-  if (e >= (c0 - r_lo) * nb) return;
-  const int r = r_lo + e / nb, c = e % nb;
-  C[r * nb + c] = T[r * ldt + c0 + c];
+  if (i < nb) T[(c0 + i) * ldt + c0 + j] = 0.5 * (C[(c0 + i) * nb + j] + C[(c0 + j) * nb + i]);
+  if (i < c0 - r_lo) C[(r_lo + i) * nb + j] = T[(r_lo + i) * ldt + c0 + j];
 }
 
 __global__ void t_beta_kernel(double* T, int ldt, int c0, int m, int nb, const double* beta) {
@@ -762,7 +843,9 @@ void tn(const TA* A, int64_t lda, int m, const TB* B, int64_t ldb, int nb, int64
   const int ct = (nb + 15) / 16;
   const int np = ct == 1 ? std::min(2, (m + 63) / 64) : 1;  // panels of 64 columns per workgroup
   const int ny = (m + 64 * np - 1) / (64 * np);
-  int G = grid_for(D, 512, std::max(64, 1024 / ny));
+  // 128 rows a workgroup (8 rounds of loads a wave) until the chip is full: at 512 rows a small space is the
+  // latency of 32 rounds on a few CUs (D = 93,710, m = 64..112: 50 -> 22 us, m = 8: 26 -> 12; D = 640: 16 -> 9)
+  int G = grid_for(D, 128, std::max(64, 1024 / ny));
   int64_t rows_per = ((D + G - 1) / G + 15) / 16 * 16;
   G = (int)((D + rows_per - 1) / rows_per);
   double* part = s.partials((size_t)G * m * nb);
@@ -779,7 +862,7 @@ void tn(const TA* A, int64_t lda, int m, const TB* B, int64_t ldb, int nb, int64
   }
 #undef TN_LAUNCH
   const int64_t len = (int64_t)m * nb;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((len + 15) / 16)), dim3(256), 0, st, part, G, len, C);
+  reduce_partials(part, G, len, C, st);
   TRBL_HIP(hipGetLastError());
 }
 
@@ -799,8 +882,7 @@ void update(const TA* A, int64_t lda, int m, const double* C, const TI* Bin, int
                        ldo, nb, D, part);
     const int64_t plen = (int64_t)m * nb;
     if (Pout)
-      hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((plen + 15) / 16)), dim3(256), 0, st, part, G, plen,
-                         Pout);
+      reduce_partials(part, G, plen, Pout, st);
     s.last_G = G;
     s.last_part = part;
     TRBL_HIP(hipGetLastError());
@@ -835,7 +917,9 @@ void update(const TA* A, int64_t lda, int m, const double* C, const TI* Bin, int
   }
   const int waves = (shm_for(8) <= 160 * 1024) ? 8 : 4;
   const size_t shm = shm_for(waves);
-  int G = grid_for(D, waves * 16 * 4, 1024);
+  // four tiles of rows a workgroup, fewer while that leaves CUs without one (D = 93,710: 15.4 us on average,
+  // 12.5 with 256 workgroups, 16.4 with one tile each, which stages C too often; D = 640: 9.0 -> 5.4)
+  int G = std::max(grid_for(D, waves * 16 * 4, 1024), grid_for(D, waves * 16, 256));
   const int64_t plen = mode == 1 ? (int64_t)m * nb : (int64_t)nb * nb;
   double* part = mode ? s.partials((size_t)G * plen) : nullptr;
   const int mi = (npan + waves - 1) / waves;  // 64-column panels per wave (mode 1)
@@ -860,8 +944,7 @@ void update(const TA* A, int64_t lda, int m, const double* C, const TI* Bin, int
 #undef UPD_LAUNCH
   if (mode) {
     if (Pout)
-      hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((plen + 15) / 16)), dim3(256), 0, st, part, G,
-                         plen, Pout);
+      reduce_partials(part, G, plen, Pout, st);
     s.last_G = G;
     s.last_part = part;
   }
@@ -893,13 +976,13 @@ void apply_small(const TI* Bin, int64_t ldi, const double* R, TO* Bout, int64_t 
 void chol(const double* part, int G, int nb, double* R, double* Rinv, const double* Rprev, double* beta, int* status,
           hipStream_t st) {
   const size_t shm = 2 * (size_t)nb * nb * sizeof(double);
-  if (G > 1) {  // sum the partials into slice 0 (each block reads its own columns before writing them)
+  if (G > 1 && nb > 8) {  // sum the partials into slice 0 (each block reads its own columns before writing them)
     const int64_t len = (int64_t)nb * nb;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((len + 15) / 16)), dim3(256), 0, st, part, G, len,
-                       const_cast<double*>(part));
+    reduce_partials(part, G, len, const_cast<double*>(part), st);
     G = 1;
   }
-  hipLaunchKernelGGL(chol_kernel, dim3(1), dim3(256), shm, st, part, G, nb, R, Rinv, Rprev, beta, status);
+  if (nb <= 16) hipLaunchKernelGGL(chol_small_kernel, dim3(1), dim3(1024), 0, st, part, G, nb, R, Rinv, Rprev, beta, status);
+  else hipLaunchKernelGGL(chol_kernel, dim3(1), dim3(256), shm, st, part, G, nb, R, Rinv, Rprev, beta, status);
   TRBL_HIP(hipGetLastError());
 }
 
@@ -978,12 +1061,9 @@ void copy_cols(const TS* src, int64_t lds_, TD* dst, int64_t ldd, int64_t D, int
   TRBL_HIP(hipGetLastError());
 }
 
-void t_alpha(double* T, int ldt, int c0, int nb, const double* C1, hipStream_t st) {
-  hipLaunchKernelGGL(t_alpha_kernel, dim3((nb * nb + 255) / 256), dim3(256), 0, st, T, ldt, c0, nb, C1);
-}
-void t_column(const double* T, int ldt, int c0, int r_lo, int nb, double* C, hipStream_t st) {
-  if (c0 <= r_lo) return;
-  hipLaunchKernelGGL(t_column_kernel, dim3(((c0 - r_lo) * nb + 255) / 256), dim3(256), 0, st, T, ldt, c0, r_lo, nb, C);
+void t_alpha(double* T, int ldt, int c0, int r_lo, int nb, double* C, hipStream_t st) {
+  const int n = std::max(nb, c0 - r_lo) * nb;
+  hipLaunchKernelGGL(t_alpha_kernel, dim3((n + 255) / 256), dim3(256), 0, st, T, ldt, c0, r_lo, nb, C);
   TRBL_HIP(hipGetLastError());
 }
 void t_beta(double* T, int ldt, int c0, int m, int nb, const double* beta, hipStream_t st) {

@@ -255,16 +255,14 @@ static int solve_t(const Model& m, const trbl_opts& o, double* evals, void* evec
     const int r_lo = k == 1 ? 0 : c0 - nb;
     if (mixed) {
       tn<float, float>((const float*)Q + c0, ldq, nb, Wq, ldq, nb, D, C1 + (size_t)c0 * nb, sc, st);
-      t_alpha(T, lm, c0, nb, C1, st);
-      t_column(T, lm, c0, r_lo, nb, C1, st);
+      t_alpha(T, lm, c0, r_lo, nb, C1, st);
       update<float, float, float>((const float*)Q + r_lo, ldq, mcur - r_lo, C1 + (size_t)r_lo * nb, Wq, ldq, Wq,
                                   ldq, nb, D, 0, nullptr, sc, st);
       tn<float, float>((const float*)Q, ldq, mcur, Wq, ldq, nb, D, C2, sc, st);
       update<float, float, float>((const float*)Q, ldq, mcur, C2, Wq, ldq, Wq, ldq, nb, D, 2, nullptr, sc, st);
     } else {
       tn<double, double>((const double*)Q + c0, ldq, nb, W, nb, nb, D, C1 + (size_t)c0 * nb, sc, st);
-      t_alpha(T, lm, c0, nb, C1, st);
-      t_column(T, lm, c0, r_lo, nb, C1, st);
+      t_alpha(T, lm, c0, r_lo, nb, C1, st);
       update<double, double>((const double*)Q + r_lo, ldq, mcur - r_lo, C1 + (size_t)r_lo * nb, W, nb, W, nb, nb, D,
                              0, nullptr, sc, st);
       tn<double, double>((const double*)Q, ldq, mcur, W, nb, nb, D, C2, sc, st);
