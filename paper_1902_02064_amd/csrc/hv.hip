@@ -23,7 +23,8 @@ static int rs_of(int C, size_t elt) { return elt == 8 ? (C >= 2 ? C + 2 : 2) : (
 // LDS bytes per row buffer of the rows kernel: 24 KB and 36 KB leave room for two workgroups per
 // CU; 144 KB is one buffer (staged and waited for at each step) for the widest source rows, so
 // that 3,952-wide sectors take a 4-column FP64 (8-column FP32) tile instead of half that
-constexpr size_t ROW_SMALL = 24 * 1024, ROW_MID = 36 * 1024, ROW_LARGE = 72 * 1024, ROW_XL = 144 * 1024;
+constexpr size_t ROW_TINY = 12 * 1024, ROW_SMALL = 24 * 1024, ROW_MID = 36 * 1024, ROW_LARGE = 72 * 1024,
+                 ROW_XL = 144 * 1024;
 
 static HVPlan& plan_for(const Model& m, int nb, size_t elt) {
   const int key = nb * 16 + (int)elt;
@@ -103,6 +104,23 @@ static HVPlan& plan_for(const Model& m, int nb, size_t elt) {
     B.nblk = (int)kv.second.size();
     B.maxdn = maxdn;
     B.items = i0.back();
+    // A row's jump groups are shared by 2, 4 or 8 parts of a workgroup where all workgroups stay resident at
+    // once: 16 KB of LDS a part, about 4096 wavefronts on 256 CUs. us per product, one part / split: sd 2+2 nb 4
+    // 40.1 / 18.6 (8), sd 3+4 nb 8 65.6 / 52.5 (4; 57.5 with 8), sd 4+5 nb 8 89.4 / 56.8 (4), sd 4+4 nb 32
+    // 127.6 / 109.3 (2); beyond, sd 6+6 nb 8 (2,772 wavefronts): 126.4 / 145.9 (2).
+    // TRBL_HV_SPLIT: the most parts (tuning override).
+    const bool tiny = B.ntb == 256 && (m.max_dn + zrows(C)) * C * elt <= ROW_TINY;
+    // two buffers of 12 KB take the LDS of one of 24 KB and hide the copies (sd 6+6: 126.4 -> 124.7 us)
+    if (tiny) B.rb_kb = 12;
+    if (tiny && (size_t)m.max_hncol * elt <= 4096) {
+      const char* env = std::getenv("TRBL_HV_SPLIT");
+      const int most = env ? std::atoi(env) : 8;
+      const int64_t waves = B.items * (B.nthr / 64);
+      for (int sp : {8, 4, 2})
+        if (B.split == 1 && sp <= most && B.nthr * sp <= 512 && B.items <= (sp == 8 ? 128 : 256 * (160 / (16 * sp + 1))) &&
+            waves * sp <= 4096)
+          B.split = sp;
+    }
     TRBL_REQUIRE(B.items < (int64_t)1 << 31 && (B.items + 7) * B.nthr < (int64_t)1 << 32, TRBL_E_INVALID,
                  "problem too large for one launch");
     B.blocks.upload(kv.second);

@@ -149,8 +149,9 @@ __device__ __forceinline__ int bank_pref(int l) {
 // chunks of one wavefront land contiguously. The row base is a buffer descriptor, the
 // wavefront's position a scalar offset and the lane's position a register that never changes,
 // so nothing the DMA reads is overwritten while it is in flight (out-of-range offsets read 0).
+// Thread tid of nthr (whole wavefronts).
 template <class T, int C>
-__device__ __forceinline__ void stage_dma(char* lds, const T* src, int64_t ld, int nrows) {
+__device__ __forceinline__ void stage_dma(char* lds, const T* src, int64_t ld, int nrows, int tid, int nthr) {
 #if defined(__HIP_DEVICE_COMPILE__)  // buffer descriptors exist only in the device pass
   using L = Tile<T, C>;
   const int total = nrows * L::CPR;
@@ -158,8 +159,8 @@ __device__ __forceinline__ void stage_dma(char* lds, const T* src, int64_t ld, i
   const int rowb = (int)(ld * (int64_t)sizeof(T));
   const int voff = (lane / L::CPR) * rowb + (lane % L::CPR) * 16;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, 0x7fffffff, 0x00020000);
-  const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
-  const int wstep = __builtin_amdgcn_readfirstlane((int)blockDim.x);
+  const int w0 = __builtin_amdgcn_readfirstlane(tid & ~63);
+  const int wstep = __builtin_amdgcn_readfirstlane(nthr);
   for (int s0 = w0; s0 < total; s0 += wstep)
     if (s0 + lane < total)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lds + (s0 << 4)), 16, voff,
@@ -169,10 +170,11 @@ __device__ __forceinline__ void stage_dma(char* lds, const T* src, int64_t ld, i
 
 // Synchronous copy into the same layout (partial or unaligned column tiles), zero beyond cvalid.
 template <class T, int C>
-__device__ __forceinline__ void stage_sync(char* lds, const T* src, int64_t ld, int nrows, int cvalid) {
+__device__ __forceinline__ void stage_sync(char* lds, const T* src, int64_t ld, int nrows, int cvalid, int tid,
+                                           int nthr) {
   using L = Tile<T, C>;
   const int total = nrows * L::CPR;
-  for (int s = threadIdx.x; s < total; s += blockDim.x) {
+  for (int s = tid; s < total; s += nthr) {
     const int r = s / L::CPR, k = s % L::CPR;
     T* d = reinterpret_cast<T*>(lds + L::at(r, k));
 #pragma unroll
@@ -227,8 +229,9 @@ __device__ __forceinline__ float signed_coef(float h, uint32_t e) {
 // sectors wider than (MP / 2) * 1024.
 constexpr bool rows_mp_fits(size_t tile_row_bytes, int mp) { return tile_row_bytes * mp <= 128; }
 // LDS bytes of the coefficient rows next to the row buffers: 16 KB where the buffers take 144 KB
-// (one workgroup per CU), else 8 KB (so that two workgroups of 72 KB buffers share a CU)
-constexpr int hs_bytes(int rbkb, bool sb) { return (sb ? rbkb : 2 * rbkb) >= 144 ? 16384 : 8192; }
+// (one workgroup per CU), else 8 KB (so that two workgroups of 72 KB buffers share a CU), 4 KB for the parts
+// of a split row
+constexpr int hs_bytes(int rbkb, bool sb) { return (sb ? rbkb : 2 * rbkb) >= 144 ? 16384 : (sb && rbkb <= 12) ? 4096 : 8192; }
 
 // acc += coef * row of the tile at `row`: the CPR chunk loads are issued together, then the FMAs.
 // Accumulator slot t holds chunk t ^ rot (rot = lane mod CPR), so that the lanes of a wavefront
@@ -288,16 +291,24 @@ __device__ __forceinline__ void gather_row(T (&acc)[C], T coef, const char* lds,
 // SB (one row buffer): the current source row is staged and waited for at every step; used
 // for narrow sectors, where half the LDS lets two workgroups share a CU and overlap each
 // other's staging, and for the 144 KB buffer of the widest rows.
-template <class T, int C, int NTB, int RBKB, bool DMA, bool SB = false, int MP = 1, int NR = 16>
-__global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
+//
+// SP > 1 (one buffer, one target a lane): the groups of a proton row, and its nn entries, are shared by SP
+// parts of a workgroup, each with a buffer, coefficients and sums of its own, added at the end in part
+// order. In a space with few proton rows a step is the latency of its chain of table, row and LDS reads on a
+// nearly empty chip, and the row's steps one after the other are the whole product (sd 2+2, 4 columns:
+// 40.1 us per product with one part, 24.3 with four, 18.6 with eight).
+template <class T, int C, int NTB, int RBKB, bool DMA, bool SB = false, int MP = 1, int NR = 16,
+          int SP = 1>
+__global__ __launch_bounds__(SP > 1 ? 512 : NTB) void hv_rows_kernel(HVArgs<T> a) {
   using L = Tile<T, C>;
   constexpr int RBYTES = RBKB * 1024;
   constexpr int HSN = hs_bytes(RBKB, SB) / (int)sizeof(T);
   constexpr int ZBASE = RBYTES / L::RB - L::NZ;  // the zero rows of each buffer: ZBASE .. ZBASE + NZ - 1
   static_assert(ZBASE + L::NZ - 1 < 65536, "row index must fit the packed jumps");
-  __shared__ __align__(256) char B0[RBYTES];
+  static_assert(SP == 1 || (SB && MP == 1), "a split row has one buffer and one target a lane");
+  __shared__ __align__(256) char B0s[SP][RBYTES];
   __shared__ __align__(256) char B1[SB ? 16 : RBYTES];
-  __shared__ __align__(16) T HS[HSN];
+  __shared__ __align__(16) T HSs[SP][HSN];
   const int64_t nitems = a.bin_item0[a.bin_nblk];
   const int64_t item = xcd_item(blockIdx.x, nitems);
   if (item >= nitems) return;
@@ -308,7 +319,11 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
   rel /= a.nchunk;
   const int ct = (int)(rel % a.ntile);
   const int pl = (int)(rel / a.ntile);
-  const int nthr = blockDim.x, tid = threadIdx.x;
+  const int nthr = blockDim.x / SP;
+  const int part = SP == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / nthr);
+  const int tid = threadIdx.x - part * nthr;
+  char* const B0 = B0s[part];
+  T* const HS = HSs[part];
   const int c0 = ct * C, cvalid = min(C, a.nb - c0);
   const int dn = a.blk_dn[b];
   const int64_t off = a.blk_off[b];
@@ -332,12 +347,14 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
 
   auto stage_row = [&](char* dst, int64_t row0, int rows) __attribute__((always_inline)) {
     const T* src = a.V + row0 * a.ldv + c0;
-    if constexpr (DMA) stage_dma<T, C>(dst, src, a.ldv, rows);
-    else stage_sync<T, C>(dst, src, a.ldv, rows, cvalid);
+    if constexpr (DMA) stage_dma<T, C>(dst, src, a.ldv, rows, tid, nthr);
+    else stage_sync<T, C>(dst, src, a.ldv, rows, cvalid, tid, nthr);
   };
 
-  const int gend = ldu(a.pg_start, gp + 1);
-  GroupIt it = group_at(a, b, ldu(a.pg_start, gp), gend);
+  const int gfirst = ldu(a.pg_start, gp), glast = ldu(a.pg_start, gp + 1);
+  const int gper = (glast - gfirst + SP - 1) / SP;  // groups of a part
+  const int gend = min(gfirst + (part + 1) * gper, glast);
+  GroupIt it = group_at(a, b, min(gfirst + part * gper, glast), gend);
   stage_row(B0, off + (int64_t)pl * dn, dn);
   if (!SB && it.cls < ncl) stage_row(B1, a.blk_off[it.sb] + (int64_t)it.p * a.blk_dn[it.sb], a.blk_dn[it.sb]);
   for (int k = tid; k < L::NZ * L::CPR; k += nthr) {  // the zero rows (above every staged row)
@@ -356,7 +373,7 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
     if (ln < thi) {
       const int sl = ns0l + ln / 64, lo = ln % 64;
       const int base = a.ne_off[sl], wd = a.ne_w[sl];
-      for (int k = 0; k < wd; k += 4) {
+      for (int k = 4 * part; k < wd; k += 4 * SP) {
         int cc[4];
         T vv[4];
 #pragma unroll
@@ -454,26 +471,8 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
       HS[e] = sum;
     }
   };
-  auto step = [&](const char* rd, char* wr) __attribute__((always_inline)) {
-    if (it.cls != cur || it.g >= hs_g0 + hs_gn) {
-      if (it.cls != cur) {
-        load_class(it.cls);
-        // also here, so that no path the compiler makes around the barrier below carries these
-        // loads into the compute phase (a wait for them there would also wait for the DMA)
-        __builtin_amdgcn_s_waitcnt(0);
-      }
-      load_hs(it.g);
-      __builtin_amdgcn_s_waitcnt(0);  // jumps in registers, HS written, before any DMA is in flight
-      __syncthreads();
-    }
-    const GroupIt nx = group_at(a, b, it.g + 1, gend);
-    if constexpr (SB) {  // the only buffer is free (every lane passed the previous barrier)
-      stage_row(B0, ldu(a.blk_off, it.sb) + (int64_t)it.p * ldu(a.blk_dn, it.sb), ldu(a.blk_dn, it.sb));
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-    } else if (nx.cls < ncl) {
-      stage_row(wr, ldu(a.blk_off, nx.sb) + (int64_t)nx.p * ldu(a.blk_dn, nx.sb), ldu(a.blk_dn, nx.sb));
-    }
+  // the step of group it, its source row at rd
+  auto compute = [&](const char* rd) __attribute__((always_inline)) {
     const T* hrow = HS + (it.g - hs_g0) * hn;
     auto coef = [&](uint32_t e) __attribute__((always_inline)) { return signed_coef(hrow[nj_op(e)], e); };
     auto rowb = [&](uint32_t e) __attribute__((always_inline)) { return nj_src(e) * L::RB; };
@@ -518,11 +517,68 @@ __global__ __launch_bounds__(NTB) void hv_rows_kernel(HVArgs<T> a) {
         }
       }
     }
+  };
+  auto step = [&](const char* rd, char* wr) __attribute__((always_inline)) {
+    if (it.cls != cur || it.g >= hs_g0 + hs_gn) {
+      if (it.cls != cur) {
+        load_class(it.cls);
+        // also here, so that no path the compiler makes around the barrier below carries these
+        // loads into the compute phase (a wait for them there would also wait for the DMA)
+        __builtin_amdgcn_s_waitcnt(0);
+      }
+      load_hs(it.g);
+      __builtin_amdgcn_s_waitcnt(0);  // jumps in registers, HS written, before any DMA is in flight
+      __syncthreads();
+    }
+    const GroupIt nx = group_at(a, b, it.g + 1, gend);
+    if constexpr (SB) {  // the only buffer is free (every lane passed the previous barrier)
+      stage_row(B0, ldu(a.blk_off, it.sb) + (int64_t)it.p * ldu(a.blk_dn, it.sb), ldu(a.blk_dn, it.sb));
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+    } else if (nx.cls < ncl) {
+      stage_row(wr, ldu(a.blk_off, nx.sb) + (int64_t)nx.p * ldu(a.blk_dn, nx.sb), ldu(a.blk_dn, nx.sb));
+    }
+    compute(rd);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     it = nx;
   };
-  if constexpr (SB) {
+  if constexpr (SP > 1) {
+    // every part takes the same number of turns, with two barriers each, whatever its groups are
+    for (int turn = 0; turn < gper; turn++) {
+      const bool on = it.cls < ncl;
+      if (on) {
+        if (it.cls != cur || it.g >= hs_g0 + hs_gn) {
+          if (it.cls != cur) load_class(it.cls);
+          load_hs(it.g);
+        }
+        stage_row(B0, ldu(a.blk_off, it.sb) + (int64_t)it.p * ldu(a.blk_dn, it.sb), ldu(a.blk_dn, it.sb));
+      }
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (on) {
+        compute(B0);
+        it = group_at(a, b, it.g + 1, gend);
+      }
+      __syncthreads();
+    }
+    if (part > 0 && tg[0] >= 0) {
+#pragma unroll
+      for (int t = 0; t < L::CPR; t++)
+        *reinterpret_cast<RowChunk<T>*>(B0 + L::at(tid, t)) = *reinterpret_cast<const RowChunk<T>*>(&acc[0][t * L::VPC]);
+    }
+    __syncthreads();
+    if (part > 0 || tg[0] < 0) return;
+#pragma unroll
+    for (int s = 1; s < SP; s++)
+#pragma unroll
+      for (int t = 0; t < L::CPR; t++) {
+        RowChunk<T> x = *reinterpret_cast<const RowChunk<T>*>(B0s[s] + L::at(tid, t));
+        const T* xv = reinterpret_cast<const T*>(&x);
+#pragma unroll
+        for (int v = 0; v < L::VPC; v++) acc[0][t * L::VPC + v] += xv[v];
+      }
+  } else if constexpr (SB) {
     while (it.cls < ncl) step(B0, B0);
   } else {
     while (it.cls < ncl) {
@@ -574,8 +630,8 @@ __global__ __launch_bounds__(NTB, NTB == 1024 ? 4 : 6) void hv_own_kernel(HVArgs
   const int tlo = tc * nthr * (MANY ? a.mp : 1);
   if (tlo >= dn) return;
   const T* src = a.V + (off + (int64_t)pl * dn) * a.ldv + c0;
-  if constexpr (DMA) stage_dma<T, C>(B0, src, a.ldv, dn);
-  else stage_sync<T, C>(B0, src, a.ldv, dn, cvalid);
+  if constexpr (DMA) stage_dma<T, C>(B0, src, a.ldv, dn, threadIdx.x, blockDim.x);
+  else stage_sync<T, C>(B0, src, a.ldv, dn, cvalid, threadIdx.x, blockDim.x);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   for (int q = 0; q < (MANY ? a.mp : 1); q++) {
@@ -704,7 +760,7 @@ __global__ __launch_bounds__(1024) void hv_cols_kernel(HVArgs<T> a) {
 template <class T, int C, int NTB, int RB, int MP = 1>
 static void launch_rows(const HVArgs<T>& a, const HVBin& B, hipStream_t s) {
   const dim3 grid((unsigned)((B.items + 7) / 8 * 8)), block(B.nthr);
-  constexpr bool SB = NTB == 256 || RB == 144;  // one buffer: narrow sectors, or the widest rows
+  constexpr bool SB = (NTB == 256 && RB != 12) || RB == 144;  // one buffer: narrow sectors, or the widest rows
   // the copy variant is a template parameter: a kernel that can take either path makes the
   // compiler wait for the DMA in flight before every LDS read
   if constexpr (MP == 1) {
@@ -718,6 +774,17 @@ static void launch_rows(const HVArgs<T>& a, const HVBin& B, hipStream_t s) {
   } else {
     if (a.dma) hipLaunchKernelGGL((hv_rows_kernel<T, C, NTB, RB, true, SB, MP, 8>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((hv_rows_kernel<T, C, NTB, RB, false, SB, MP, 8>), grid, block, 0, s, a);
+  }
+}
+template <class T, int C, int SP>
+static void launch_split(const HVArgs<T>& a, const HVBin& B, hipStream_t s) {
+  const dim3 grid((unsigned)((B.items + 7) / 8 * 8)), block(B.nthr * SP);
+  if (B.nr == 32) {
+    if (a.dma) hipLaunchKernelGGL((hv_rows_kernel<T, C, 256, 12, true, true, 1, 32, SP>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((hv_rows_kernel<T, C, 256, 12, false, true, 1, 32, SP>), grid, block, 0, s, a);
+  } else {
+    if (a.dma) hipLaunchKernelGGL((hv_rows_kernel<T, C, 256, 12, true, true, 1, 16, SP>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((hv_rows_kernel<T, C, 256, 12, false, true, 1, 16, SP>), grid, block, 0, s, a);
   }
 }
 template <class T, int C, int MP>
@@ -769,7 +836,11 @@ static void dispatch_c(HVArgs<T>& a, const HVPlan& P, hipStream_t s, int parts, 
    : B.rb_kb == 36 ? launch_rows<T, C, NTB, 36>(a, B, s)                    \
    : B.rb_kb == 72 ? launch_rows<T, C, NTB, 72>(a, B, s)                    \
                    : launch_rows<T, C, NTB, 144>(a, B, s))
-    if (B.ntb == 256) TRBL_ROWS_RB(256);
+    if (B.split == 8) launch_split<T, C, 8>(a, B, s);
+    else if (B.split == 4) launch_split<T, C, 4>(a, B, s);
+    else if (B.split == 2) launch_split<T, C, 2>(a, B, s);
+    else if (B.ntb == 256 && B.rb_kb == 12) launch_rows<T, C, 256, 12>(a, B, s);
+    else if (B.ntb == 256) TRBL_ROWS_RB(256);
     else if (B.ntb == 768) TRBL_ROWS_RB(768);
     else if (B.mp == 4) {
       if constexpr (rows_mp_fits(C * sizeof(T), 4)) {

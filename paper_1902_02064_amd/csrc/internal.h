@@ -163,6 +163,7 @@ struct HVBin {
   int mp = 1;                                                    // targets per lane (1024-wide, 72 KB bins)
   int nr = 16;                                                   // neutron jumps per class held in registers
   int maxdn = 0;                                                 // widest target sector of the bin
+  int split = 1;                                                 // parts of a workgroup that share a row's jump groups
   int64_t items = 0;
   DevBuf blocks, item0;  // block ids of the bin, first work item of each (nblk + 1)
 };
