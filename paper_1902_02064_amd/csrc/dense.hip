@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void tn_partial_kernel(const TA* __restrict__ 
   const int64_t r0 = (int64_t)blockIdx.x * rows_per;
   const int64_t r1 = min(D, r0 + rows_per);
   const int li = lane & 15, lk = lane >> 4;
-  // (two row quads in flight per wave: a small space gains a few us, a basis that streams from HBM reads 5 % slower
+  // (two row quads in flight per wave: a small space gains 1 to 2 us, a basis that streams from HBM reads 5 % slower
   // in FP64 and 19 % in FP32)
   for (int64_t r = r0 + 4 * wave; r < r1; r += 4 * WAVES) {
     const int64_t rr = r + lk;
@@ -839,7 +839,7 @@ void tn(const TA* A, int64_t lda, int m, const TB* B, int64_t ldb, int nb, int64
   const int np = ct == 1 ? std::min(2, (m + 63) / 64) : 1;  // panels of 64 columns per workgroup
   const int ny = (m + 64 * np - 1) / (64 * np);
   // 128 rows a workgroup (8 rounds of loads a wave) until the chip is full: at 512 rows a small space is the
-  // latency of 32 rounds on a few CUs (D = 93,710, m = 64..112: 50 -> 22 us, m = 8: 26 -> 12; D = 640: 16 -> 9)
+  // latency of 32 rounds on a few CUs (D = 93,710, m = 64..112: 50 -> 24 us, m = 8: 26 -> 12; D = 640: 16 -> 10)
   int G = grid_for(D, 128, std::max(64, 1024 / ny));
   int64_t rows_per = ((D + G - 1) / G + 15) / 16 * 16;
   G = (int)((D + rows_per - 1) / rows_per);
