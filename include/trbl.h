@@ -196,6 +196,10 @@ int trbl_solve(const trbl_model* m, const trbl_opts* opts, double* evals, void* 
    trbl_set_hamiltonian list (grad_v, host n_v) and optionally the proton then neutron
    single-particle energies (grad_spe, host 2*n_orbits, may be NULL).
    evecs: device [D][n_eig] FP64 eigenvectors; NULL = recompute them with trbl_solve(opts).
+   The first gradient of a model builds tables on the device that the model keeps until it is destroyed (they
+   depend on the space alone): 8 bytes for every pair of nucleons of every stored determinant of a species,
+   4 bytes for every m-state of every set of n - 1 nucleons of a species where there are two, and 16 bytes a
+   work item. TRBL_E_NOMEM if they do not fit.
    TRBL_E_INVALID for single-species spaces that generate their operator per element. */
 int trbl_tbme_grad(const trbl_model* m, const trbl_opts* opts, int n_eig, const double* w,
                    const void* evecs, double* grad_v, double* grad_spe);

@@ -29,14 +29,19 @@ namespace {
 constexpr int GRAD_MAXPAIR = 1024;  // pairs of one block: at most 64 states x 16 orbits of one m
 
 // One work item: a core and a run of the states it is combined with (pn: neutron cores of one group,
-// identical particles: states of the other species in one block).
+// identical particles: states of the other species in one block; core is the index of the core's list).
 struct GradItem {
   int rect, core, first, count;
 };
 // What a run of items shares. pn: pair block and first entry of the target blocks of its pairs;
-// identical particles: pair block, first pair in the pair-major core table, product block, 0.
+// identical particles: pair block and product block.
 struct GradRect {
   int k, list, blk, pad;
+};
+// Identical particles: a pair outside a core (its index in the pair block) and the state that they form
+// (index in its sector << 1 | sign).
+struct GradPair {
+  int id, state;
 };
 
 struct GradArgs {
@@ -55,9 +60,11 @@ struct GradArgs {
   const int* rblk;   // target block of each pair (-1: none)
   const int* rkp;    // [core * ns + state]: position of state << 24 | local index of core + state, -1 inside
   const int* rkn;
-  // identical particles: [core * pairs + pair]: local index of core + pair << 1 | sign, -1 where they overlap
-  const int* rk2;
-  int npair, species;
+  // identical particles: the pairs outside a core that reach one sector are list_pair[list_off[core] ..
+  // list_off[core + 1])
+  const int* list_off;
+  const GradPair* list_pair;
+  int species;
 };
 
 typedef double v2d __attribute__((ext_vector_type(2)));
@@ -167,7 +174,7 @@ __device__ __forceinline__ void dens_add(const GradArgs& a, const GradRect& rc, 
   double* rho = a.rho + a.rho_off[rc.k];
   for (int e = threadIdx.x; e < R * R; e += 256) {
     const int i = i0 + e / R, j = j0 + e % R;
-    if (i <= j && j < d) atomicAdd(rho + (int64_t)id[i] * D2 + id[j], red[e]);
+    if (i <= j && j < d) atomicAdd(rho + (int64_t)min(id[i], id[j]) * D2 + max(id[i], id[j]), red[e]);
   }
   __syncthreads();
 }
@@ -188,32 +195,33 @@ __global__ __launch_bounds__(256, 4) void dens_kernel(GradArgs a, int maxpair) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   int64_t stride = 1;  // rows between consecutive states of the run
   if (!PN && a.species == 1) stride = a.blk_dn[rc.blk];
-  if (w == 0) {  // the pairs outside the core, in order
+  if constexpr (!PN) {  // the pairs outside the core are listed
+    const int e0 = a.list_off[it.core], d = a.list_off[it.core + 1] - e0;
+    const int64_t off = a.blk_off[rc.blk], rs = a.species == 0 ? a.blk_dn[rc.blk] : 1;
+    for (int i = threadIdx.x; i < d; i += 256) {
+      const GradPair p = a.list_pair[e0 + i];
+      row[i] = off + (p.state >> 1) * rs;
+      id[i] = p.id;
+      us[i] = 0;
+      sg[i] = p.state & 1;
+    }
+    if (threadIdx.x == 0) nd = d;
+  } else if (w == 0) {  // the pairs outside the core, in order
     int d = 0;
     for (int e0 = 0; e0 < D2; e0 += 64) {
       const int e = min(e0 + l, D2 - 1);
       bool ok = e0 + l < D2;
       int64_t r0 = 0;
-      int u = 0, s = 0;
-      if constexpr (PN) {
-        const int xu = a.pr_xu[q0 + e], b = a.rblk[rc.list + e], rp = a.rkp[it.core * a.ns + (xu & 255)];
-        ok = ok && b >= 0 && rp >= 0;
-        if (ok) r0 = a.blk_off[b] + (int64_t)(rp & 0xFFFFFF) * a.blk_dn[b];
-        u = xu >> 8;
-        s = rp >> 24;
-      } else {
-        const int r = a.rk2[(int64_t)it.core * a.npair + rc.list + e];
-        ok = ok && r >= 0;
-        if (ok) r0 = a.blk_off[rc.blk] + (int64_t)(r >> 1) * (a.species == 0 ? a.blk_dn[rc.blk] : 1);
-        s = r & 1;
-      }
+      const int xu = a.pr_xu[q0 + e], b = a.rblk[rc.list + e], rp = a.rkp[it.core * a.ns + (xu & 255)];
+      ok = ok && b >= 0 && rp >= 0;
+      if (ok) r0 = a.blk_off[b] + (int64_t)(rp & 0xFFFFFF) * a.blk_dn[b];
       const uint64_t mask = __ballot(ok);
       if (ok) {
         const int i = d + __popcll(mask & ((1ull << l) - 1));
         row[i] = r0;
         id[i] = e0 + l;
-        us[i] = u;
-        sg[i] = s;
+        us[i] = xu >> 8;
+        sg[i] = rp >> 24;
       }
       d += __popcll(mask);
     }
@@ -291,11 +299,19 @@ __global__ __launch_bounds__(256) void dens_occ_kernel(OccArgs a, int64_t D) {
   if (t < 32 && (t & 15) < a.norb) atomicAdd(a.occ + (t >> 4) * a.norb + (t & 15), sum[t]);
 }
 
-// Pair lists, cores and work items of one channel (0 pp, 1 nn, 2 pn): they depend on the space alone.
+// Pair blocks of one channel (0 pp, 1 nn, 2 pn): they depend on the space alone.
 struct Channel {
   std::vector<int> pid, pblk;             // [a * ns + b]: index in its block, block (-1: none)
   std::vector<int> pr_off, rho_off;
-  std::vector<int> pr_xu, rblk, rk[2], rk2;
+  std::vector<int> pr_xu;
+  size_t nitems = 0;
+};
+
+// Cores and work items of one channel while they are built for the device.
+struct ChannelWork {
+  std::vector<int> rblk, rk[2];           // pn
+  std::vector<int> list_off;              // identical particles
+  std::vector<GradPair> list_pair;
   std::vector<GradRect> rect;
   std::vector<GradItem> items;
 };
@@ -379,9 +395,8 @@ std::vector<int> sector_map(const Model& m, std::map<std::pair<int, int>, int> (
   return bos;
 }
 
-Channel pn_channel(const Model& m) {
-  Channel ch;
-  if (m.n_prot == 0 || m.n_neut == 0) return ch;
+void pn_channel(const Model& m, Channel& ch, ChannelWork& cw) {
+  if (m.n_prot == 0 || m.n_neut == 0) return;
   const int ns = m.ns;
   std::map<std::pair<int, int>, int> kid, secid[2];
   pair_blocks(m, false, ch, kid);
@@ -391,7 +406,7 @@ Channel pn_channel(const Model& m) {
   for (int s = 0; s < 2; s++) {
     std::vector<uint64_t> words;
     groups[s] = core_groups(m, m.sp[s].npart - 1, words);
-    ch.rk[s].assign(words.size() * ns, -1);
+    cw.rk[s].assign(words.size() * ns, -1);
     for (size_t q = 0; q < words.size(); q++)
       for (int st = 0; st < ns; st++) {
         if ((words[q] >> st) & 1) continue;
@@ -399,77 +414,148 @@ Channel pn_channel(const Model& m) {
         if (at == m.sp[s].index.end()) continue;  // its sector is in no block
         const int loc = at->second - m.sp[s].sectors[m.sp[s].sector_of[at->second]].start;
         TRBL_REQUIRE(loc < (1 << 24), TRBL_E_INVALID, "sector too large for the gradient tables");
-        ch.rk[s][q * ns + st] = __builtin_popcountll(words[q] & ((1ull << st) - 1)) << 24 | loc;
+        cw.rk[s][q * ns + st] = __builtin_popcountll(words[q] & ((1ull << st) - 1)) << 24 | loc;
       }
   }
+  // rectangles of core groups whose pair block reaches some block of the space
+  struct Rect {
+    const CoreGroup *p, *n;
+  };
+  std::vector<Rect> of;
   for (const CoreGroup& gp : groups[0])
     for (const CoreGroup& gn : groups[1])
       for (int odd = 0; odd < 2; odd++) {
         const auto k = kid.find({m.twoM - gp.tm - gn.tm, odd});
         if (k == kid.end()) continue;
         bool any = false;
-        const int list = (int)ch.rblk.size();
+        const int list = (int)cw.rblk.size();
         for (int e = ch.pr_off[k->second]; e < ch.pr_off[k->second + 1]; e++) {
           const int x = ch.pr_xu[e] & 255, u = ch.pr_xu[e] >> 8;
           const auto ip = secid[0].find({gp.tm + m.st_tm[x], gp.par ^ (m.orbits[m.st_orb[x]].l & 1)});
           const auto in = secid[1].find({gn.tm + m.st_tm[u], gn.par ^ (m.orbits[m.st_orb[u]].l & 1)});
           const int b = ip != secid[0].end() && in != secid[1].end() ? bos[ip->second * nnsec + in->second] : -1;
-          ch.rblk.push_back(b);
+          cw.rblk.push_back(b);
           any = any || b >= 0;
         }
         if (!any) {
-          ch.rblk.resize(list);
+          cw.rblk.resize(list);
           continue;
         }
-        const int r = (int)ch.rect.size();
-        ch.rect.push_back({k->second, list, 0, 0});
-        for (int cp = gp.start; cp < gp.start + gp.count; cp++)
-          for (int n0 = 0; n0 < gn.count; n0 += 256)
-            ch.items.push_back({r, cp, gn.start + n0, std::min(256, gn.count - n0)});
+        cw.rect.push_back({k->second, list, 0, 0});
+        of.push_back({&gp, &gn});
       }
-  return ch;
+  // up to 256 neutron cores an item, more where that would take more than 2^24 items
+  int chunk = 256;
+  auto total = [&] {
+    size_t t = 0;
+    for (const Rect& r : of) t += (size_t)r.p->count * ((r.n->count + chunk - 1) / chunk);
+    return t;
+  };
+  while (chunk < (1 << 20) && total() > (size_t)1 << 24) chunk *= 2;
+  cw.items.reserve(total());
+  for (size_t r = 0; r < of.size(); r++)
+    for (int cp = of[r].p->start; cp < of[r].p->start + of[r].p->count; cp++)
+      for (int n0 = 0; n0 < of[r].n->count; n0 += chunk)
+        cw.items.push_back({(int)r, cp, of[r].n->start + n0, std::min(chunk, of[r].n->count - n0)});
 }
 
-Channel identical_channel(const Model& m, int s) {
-  Channel ch;
+// Words numbered in the order of their first appearance.
+class WordIndex {
+ public:
+  int at(uint64_t w) {
+    if (2 * (words.size() + 1) > slot_.size()) grow();
+    size_t h = home(w);
+    while (slot_[h] >= 0 && words[slot_[h]] != w) h = (h + 1) & (slot_.size() - 1);
+    if (slot_[h] < 0) {
+      slot_[h] = (int)words.size();
+      words.push_back(w);
+    }
+    return slot_[h];
+  }
+  std::vector<uint64_t> words;
+
+ private:
+  size_t home(uint64_t w) const { return (size_t)((w * 0x9E3779B97F4A7C15ull) >> 20) & (slot_.size() - 1); }
+  void grow() {
+    slot_.assign(std::max<size_t>(256, 2 * slot_.size()), -1);
+    for (size_t i = 0; i < words.size(); i++) {
+      size_t h = home(words[i]);
+      while (slot_[h] >= 0) h = (h + 1) & (slot_.size() - 1);
+      slot_[h] = (int)i;
+    }
+  }
+  std::vector<int> slot_;
+};
+
+// The lists come from the states that the space stores: every pair of a state's nucleons belongs to the core of
+// the others, so that the tables hold C(n, 2) entries a state, whatever the number of subsets of the m-states
+// (28 protons in 32 states: 0.6 million entries, against 906,192 cores x 496 pairs).
+void identical_channel(const Model& m, int s, Channel& ch, ChannelWork& cw) {
   const Species& S = m.sp[s];
-  if (S.npart < 2) return ch;
+  if (S.npart < 2) return;
   const int ns = m.ns;
   std::map<std::pair<int, int>, int> kid;
   pair_blocks(m, true, ch, kid);
-  std::vector<uint64_t> words;
-  const std::vector<CoreGroup> groups = core_groups(m, S.npart - 2, words);
-  const int np = ch.pr_off.back();
-  ch.rk2.assign(words.size() * (size_t)np, -1);
-  for (size_t q = 0; q < words.size(); q++)
-    for (int e = 0; e < np; e++) {
-      const int a = ch.pr_xu[e] & 255, b = ch.pr_xu[e] >> 8;
-      const uint64_t pair = 1ull << a | 1ull << b;
-      if (words[q] & pair) continue;
-      const auto at = S.index.find(words[q] | pair);
-      if (at == S.index.end()) continue;
-      const int loc = at->second - S.sectors[S.sector_of[at->second]].start;
-      ch.rk2[q * np + e] = loc << 1 | (below_odd(words[q], a) ^ below_odd(words[q], b));
+  // product blocks of every sector; sectors in none of them are left out
+  std::vector<std::vector<int>> blocks(S.sectors.size());
+  for (size_t b = 0; b < m.blocks.size(); b++)
+    if ((s == 0 ? m.blocks[b].dn : m.blocks[b].dp) > 0)
+      blocks[s == 0 ? m.blocks[b].psec : m.blocks[b].nsec].push_back((int)b);
+  cw.list_off.assign(1, 0);
+  for (size_t q = 0; q < S.sectors.size(); q++) {
+    if (blocks[q].empty()) continue;
+    const SpeciesSector& sec = S.sectors[q];
+    // entries of the sector, then by core in the order of the states. A core fixes the (2M, parity) of the
+    // pair that completes it to the sector, so its list belongs to one pair block.
+    struct Entry {
+      int core;
+      GradPair p;
+    };
+    WordIndex cores;
+    std::vector<int> kblk, count;
+    std::vector<Entry> entry;
+    entry.reserve((size_t)sec.size * S.npart * (S.npart - 1) / 2);
+    for (int g = 0; g < sec.size; g++) {
+      const uint64_t w = S.words[sec.start + g];
+      for (uint64_t x = w; x; x &= x - 1) {
+        const int a = __builtin_ctzll(x);
+        for (uint64_t y = x & (x - 1); y; y &= y - 1) {
+          const int b = __builtin_ctzll(y);
+          const uint64_t core = w ^ (1ull << a) ^ (1ull << b);
+          const int c = cores.at(core);
+          if (c == (int)kblk.size()) {
+            kblk.push_back(ch.pblk[a * ns + b]);
+            count.push_back(0);
+          }
+          count[c]++;
+          entry.push_back({c, {ch.pid[a * ns + b], g << 1 | (below_odd(core, a) ^ below_odd(core, b))}});
+        }
+      }
     }
-  for (const CoreGroup& g : groups)
-    for (size_t b = 0; b < m.blocks.size(); b++) {
-      const SpeciesSector& sec = S.sectors[s == 0 ? m.blocks[b].psec : m.blocks[b].nsec];
-      const auto k = kid.find({sec.twoM - g.tm, (sec.par < 0 ? 1 : 0) ^ g.par});
+    const size_t base = cw.list_pair.size(), l0 = cw.list_off.size() - 1;
+    TRBL_REQUIRE(base + entry.size() < ((size_t)1 << 31), TRBL_E_NOMEM, "too many states for the gradient tables");
+    for (int c : count) cw.list_off.push_back(cw.list_off.back() + c);
+    cw.list_pair.resize(base + entry.size());
+    std::vector<int> next(cw.list_off.begin() + l0, cw.list_off.end() - 1);
+    for (const Entry& e : entry) cw.list_pair[next[e.core]++] = e.p;
+    for (int b : blocks[q]) {
       const int other = s == 0 ? m.blocks[b].dn : m.blocks[b].dp;
-      if (k == kid.end() || other == 0) continue;
-      const int r = (int)ch.rect.size();
-      ch.rect.push_back({k->second, ch.pr_off[k->second], (int)b, 0});
-      for (int q = g.start; q < g.start + g.count; q++)
-        for (int o = 0; o < other; o += 1024) ch.items.push_back({r, q, o, std::min(1024, other - o)});
+      std::map<int, int> rect_of;  // pair block -> rectangle
+      for (size_t c = 0; c < kblk.size(); c++) {
+        const auto r = rect_of.emplace(kblk[c], (int)cw.rect.size());
+        if (r.second) cw.rect.push_back({kblk[c], 0, b, 0});
+        for (int o = 0; o < other; o += 1024)
+          cw.items.push_back({r.first->second, (int)(l0 + c), o, std::min(1024, other - o)});
+      }
     }
-  return ch;
+  }
 }
 
 }  // namespace
 
 struct GradTables {
   Channel ch[3];
-  DevBuf pr_off[3], rho_off[3], pr_xu, rblk, rk[2], rk2[2], rect[3], items[3];
+  DevBuf pr_off[3], rho_off[3], pr_xu, rblk, rk[2], list_off[2], list_pair[2], rect[3], items[3];
   DevBuf work;  // weights, then the densities of the three channels and the occupations
 };
 
@@ -479,19 +565,23 @@ void GradTablesDelete::operator()(GradTables* t) const { delete t; }
 static GradTables& tables_for(const Model& m) {
   if (m.grad_tables) return *m.grad_tables;
   std::unique_ptr<GradTables, GradTablesDelete> t(new GradTables());
-  for (int s = 0; s < 2; s++) t->ch[s] = identical_channel(m, s);
-  t->ch[2] = pn_channel(m);
   for (int k = 0; k < 3; k++) {
+    ChannelWork cw;
+    if (k == 2) pn_channel(m, t->ch[k], cw);
+    else identical_channel(m, k, t->ch[k], cw);
+    t->ch[k].nitems = cw.items.size();
     t->pr_off[k].upload(t->ch[k].pr_off);
     t->rho_off[k].upload(t->ch[k].rho_off);
-    t->rect[k].upload(t->ch[k].rect);
-    t->items[k].upload(t->ch[k].items);
-  }
-  t->pr_xu.upload(t->ch[2].pr_xu);
-  t->rblk.upload(t->ch[2].rblk);
-  for (int s = 0; s < 2; s++) {
-    t->rk[s].upload(t->ch[2].rk[s]);
-    t->rk2[s].upload(t->ch[s].rk2);
+    t->rect[k].upload(cw.rect);
+    t->items[k].upload(cw.items);
+    if (k == 2) {
+      t->pr_xu.upload(t->ch[k].pr_xu);
+      t->rblk.upload(cw.rblk);
+      for (int s = 0; s < 2; s++) t->rk[s].upload(cw.rk[s]);
+    } else {
+      t->list_off[k].upload(cw.list_off);
+      t->list_pair[k].upload(cw.list_pair);
+    }
   }
   m.grad_tables = std::move(t);
   return *m.grad_tables;
@@ -526,7 +616,7 @@ void tbme_gradient(const Model& m, int n_eig, const double* w, const double* X, 
   a.rkp = t.rk[0].as<int>();
   a.rkn = t.rk[1].as<int>();
   for (int k = 2; k >= 0; k--) {
-    const size_t ni = t.ch[k].items.size();
+    const size_t ni = t.ch[k].nitems;
     if (ni == 0) continue;
     a.items = t.items[k].as<GradItem>();
     a.rect = t.rect[k].as<GradRect>();
@@ -535,8 +625,8 @@ void tbme_gradient(const Model& m, int n_eig, const double* w, const double* X, 
     a.rho = work + at[k];
     a.species = k;
     if (k < 2) {
-      a.rk2 = t.rk2[k].as<int>();
-      a.npair = t.ch[k].pr_off.back();
+      a.list_off = t.list_off[k].as<int>();
+      a.list_pair = t.list_pair[k].as<GradPair>();
     }
     int maxpair = 0;  // widest block, in whole wavefronts
     for (size_t b = 0; b + 1 < t.ch[k].pr_off.size(); b++)
@@ -576,7 +666,7 @@ void tbme_gradient(const Model& m, int n_eig, const double* w, const double* X, 
   const std::vector<std::vector<std::pair<int, double>>>* coef[3] = {&m.coef_pp, &m.coef_nn, &m.coef_pn};
   for (int k = 0; k < 3; k++) {
     const Channel& ch = t.ch[k];
-    if (ch.items.empty()) continue;
+    if (ch.nitems == 0) continue;
     for (size_t q = 0; q < terms[k]->size(); q++) {
       const MTerm& u = (*terms[k])[q];  // c+_a c+_b c_d c_c (pn: a, c protons)
       const int blk = ch.pblk[u.a * ns + u.b], D2 = ch.pr_off[blk + 1] - ch.pr_off[blk];
