@@ -20,8 +20,9 @@
 // Slots. The proton cores are worked through in batches. A batch owns a slot row for every
 // (core K_p, x, position of u in the target's neutron word, target neutron state), so each slot is
 // written exactly once, and the target rows K_p + x then add their slots to W in a fixed order:
-// no atomics, and the result does not depend on scheduling. Two slot buffers alternate: one launch
-// computes a batch and adds the previous one to W.
+// no atomics, and the result does not depend on scheduling. With several batches two slot buffers
+// alternate: one launch computes a batch and adds the previous one to W. With one batch the slots of
+// all targets lie position pair by position pair, and the own-row kernel or pn_sum_kernel adds them.
 #include <algorithm>
 #include <array>
 #include <cstdlib>
@@ -70,46 +71,67 @@ struct PNTileArgs {
 
 constexpr int RED_ROWS = 64;  // target rows of one reducing workgroup
 
-// W[row + t][c0 + c] += the slots of target row t, entry by entry and position by position
-template <class T>
-__device__ __forceinline__ void add_slots(const PNTileArgs<T>& a, int bid) {
+// 16 bytes of a row of W += the `per` slots of each of n entries (first slot chunk z(i), `step` chunks apart),
+// entry by entry
+template <class T, class F>
+__device__ __forceinline__ void add_chunk(const PNTileArgs<T>& a, int64_t row, int k, int n, int per, int64_t step,
+                                          F&& z) {
   constexpr int VPC = 16 / (int)sizeof(T);  // values per 16 bytes
   typedef T zv __attribute__((ext_vector_type(VPC)));
+  T* w = a.W + row * a.ldw + a.c0 + VPC * k;
+  const bool full = a.wvec && VPC * k + VPC <= a.cval;
+  zv v;
+  if (full) {
+    v = *reinterpret_cast<const zv*>(w);
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPC; j++) v[j] = VPC * k + j < a.cval ? w[j] : T(0);
+  }
+  for (int i = 0; i < n; i++) {
+    const zv* x = reinterpret_cast<const zv*>(a.Zr) + z(i) + k;
+    int q = 0;
+    for (; q + 4 <= per; q += 4) {  // four in flight
+      zv zq[4];
+#pragma unroll
+      for (int j = 0; j < 4; j++) zq[j] = __builtin_nontemporal_load(x + (q + j) * step);
+#pragma unroll
+      for (int j = 0; j < 4; j++) v += zq[j];
+    }
+    for (; q < per; q++) v += __builtin_nontemporal_load(x + q * step);
+  }
+  if (full) {
+    *reinterpret_cast<zv*>(w) = v;
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPC; j++)
+      if (VPC * k + j < a.cval) w[j] = v[j];
+  }
+}
+
+// the slots of the target rows of a batch, entry by entry and position by position
+template <class T>
+__device__ __forceinline__ void add_slots(const PNTileArgs<T>& a, int bid) {
   const int ri = bid / a.nchunk, t0 = (bid % a.nchunk) * RED_ROWS;
   if (ri >= a.nrows) return;
   const PNRow r = a.rows[ri];
   const int n = min(RED_ROWS, r.dn - t0) * a.cprv;  // not positive: a chunk beyond this row
-  const int64_t step = (int64_t)(a.zstep ? a.zstep : r.dn) * a.cpr;
+  const int64_t step = (int64_t)r.dn * a.cpr;
   for (int e = threadIdx.x; e < n; e += 256) {
-    const int t = t0 + e / a.cprv, k = e % a.cprv;
-    T* w = a.W + (r.row + t) * a.ldw + a.c0 + VPC * k;
-    const bool full = a.wvec && VPC * k + VPC <= a.cval;
-    zv v;
-    if (full) {
-      v = *reinterpret_cast<const zv*>(w);
-    } else {
-#pragma unroll
-      for (int j = 0; j < VPC; j++) v[j] = VPC * k + j < a.cval ? w[j] : T(0);
-    }
-    for (int i = 0; i < r.ne; i++) {
-      const zv* z = reinterpret_cast<const zv*>(a.Zr) + ((int64_t)a.tent[r.e0 + i] + t) * a.cpr + k;
-      int q = 0;
-      for (; q + 4 <= a.nneut; q += 4) {  // four in flight
-        zv zq[4];
-#pragma unroll
-        for (int j = 0; j < 4; j++) zq[j] = __builtin_nontemporal_load(z + (q + j) * step);
-#pragma unroll
-        for (int j = 0; j < 4; j++) v += zq[j];
-      }
-      for (; q < a.nneut; q++) v += __builtin_nontemporal_load(z + q * step);
-    }
-    if (full) {
-      *reinterpret_cast<zv*>(w) = v;
-    } else {
-#pragma unroll
-      for (int j = 0; j < VPC; j++)
-        if (VPC * k + j < a.cval) w[j] = v[j];
-    }
+    const int t = t0 + e / a.cprv;
+    add_chunk(a, r.row + t, e % a.cprv, r.ne, a.nneut, step,
+              [&](int i) { return ((int64_t)a.tent[r.e0 + i] + t) * a.cpr; });
+  }
+}
+
+// One batch: every target has the same number of slots, `zstep` slot rows apart, so a thread takes 16 bytes of
+// any row (a workgroup a target row leaves most of its threads idle where the rows have few neutron states:
+// pf 5+1, 32 columns FP64, 28.5 us against 6.7 us a tile).
+template <class T>
+__global__ __launch_bounds__(256) void pn_sum_kernel(PNTileArgs<T> a, int rows, int slots) {
+  const int64_t step = (int64_t)rows * a.cpr;  // all slots together stay below 4 GiB
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < rows * a.cprv; e += gridDim.x * 256) {
+    const int t = e / a.cprv;
+    add_chunk(a, t, e - t * a.cprv, 1, slots, step, [&](int) { return (int64_t)t * a.cpr; });
   }
 }
 
@@ -587,7 +609,7 @@ void build_pn_tiles(Model& m) {
           const int b = z;
           const int r = rk[0][(size_t)cp * ns + x], pl = r & 0xFFFFFF, dn = m.blocks[b].dn;
           z = (int)(T.zstep ? (int64_t)(r >> 24) * m.n_neut * m.dim + m.blocks[b].off + (int64_t)pl * dn : at);
-          to[blk_row0[b] + pl].push_back(z);
+          if (nbat > 1) to[blk_row0[b] + pl].push_back(z);
           at += (int64_t)m.n_neut * dn;
         }
     size_t b = 0;
@@ -600,8 +622,8 @@ void build_pn_tiles(Model& m) {
     }
     B.nitems = (int)(items.size() / 4) - B.item0;
     B.nrows = (int)trow.size() - B.row0;
-    TRBL_REQUIRE(B.nitems < (1 << 22) && B.nrows < (1 << 22) / ((B.maxdn + RED_ROWS - 1) / RED_ROWS), TRBL_E_INVALID,
-                 "too many core pairs for one launch");
+    const int64_t nred = (int64_t)B.nrows * ((B.maxdn + RED_ROWS - 1) / RED_ROWS);  // reducing workgroups
+    TRBL_REQUIRE(B.nitems < (1 << 22) && nred < (1 << 22), TRBL_E_INVALID, "too many core pairs for one launch");
     if (B.nitems > 0) T.batches.push_back(B);
   }
   TRBL_REQUIRE(items.size() < ((size_t)1 << 31), TRBL_E_INVALID, "too many core pairs");
@@ -635,7 +657,8 @@ void build_pn_tiles(Model& m) {
 }
 
 template <class T, int VPL, int KN>
-static void run_batches(const PNTiles& P, PNTileArgs<T>& a, bool big, bool reduce, hipStream_t s) {
+static void run_batches(const Model& m, PNTileArgs<T>& a, bool big, bool reduce, hipStream_t s) {
+  const PNTiles& P = m.pn;
   const int ks = (P.max_pairs + 7) / 8 * 2;
   const size_t shm = (size_t)((ks + 3) / 4 * ks) * 64 * sizeof(T);
   const int4* items = P.items.as<int4>();
@@ -646,6 +669,12 @@ static void run_batches(const PNTiles& P, PNTileArgs<T>& a, bool big, bool reduc
   const int n = (int)P.batches.size();
   for (int i = 0; i < n + (reduce ? 1 : 0); i++) {
     a.nred = a.nitems = 0;
+    if (n == 1 && i == 1) {
+      a.Zr = reinterpret_cast<const T*>(z);
+      hipLaunchKernelGGL(pn_sum_kernel<T>, dim3(elementwise_grid(m.dim * a.cprv)), dim3(256), 0, s, a, (int)m.dim,
+                         m.n_prot * m.n_neut);
+      break;
+    }
     if (i > 0) {
       const PNTiles::Batch& R = P.batches[i - 1];
       a.nchunk = (R.maxdn + RED_ROWS - 1) / RED_ROWS;
@@ -711,13 +740,13 @@ void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int6
     a.cpr = pn_slot_stride(sizeof(T), a.cval);
     if (a.cval < VPC) {
       a.lr = VPC;  // one value a lane
-      run_batches<T, 1, 16 / VPC>(P, a, big, reduce, s);
+      run_batches<T, 1, 16 / VPC>(m, a, big, reduce, s);
       continue;
     }
     a.lr = a.cpr;
-    if (a.lr <= 2) run_batches<T, VPC, 8>(P, a, big, reduce, s);
-    else if (a.lr <= 4) run_batches<T, VPC, 4>(P, a, big, reduce, s);
-    else run_batches<T, VPC, 2>(P, a, big, reduce, s);
+    if (a.lr <= 2) run_batches<T, VPC, 8>(m, a, big, reduce, s);
+    else if (a.lr <= 4) run_batches<T, VPC, 4>(m, a, big, reduce, s);
+    else run_batches<T, VPC, 2>(m, a, big, reduce, s);
   }
   TRBL_HIP(hipGetLastError());
 }
