@@ -185,13 +185,14 @@ struct PNTiles {
   bool on = false;
   bool force = false;        // in every space that allows them (TRBL_PN_TILES=2)
   bool one_tile = false;     // only for products of one column tile (128-byte rows)
+  bool swap = false;         // items fix a neutron core and run over proton cores
   int max_pairs = 0;         // widest pair block
   DevBuf rk[2];              // [core * ns + state]: position of state << 24 | local index of core + state, -1 inside
   DevBuf pr_off, pr_xu;      // pair blocks: x | u << 8
   DevBuf hb_off, hb, hb32;   // per pair block: D2 x D2 matrix (FP64, FP32), row = target pair
   DevBuf rect, rblk;         // rectangles (pair block, rblk start), per rectangle and pair the target block << 1 |
                              // parity of its neutron sector (-1: none)
-  DevBuf items;              // work items, batch by batch (rectangle, proton core, first neutron core, count)
+  DevBuf items;              // work items, batch by batch (rectangle, fixed core, first core of the run, count)
   DevBuf boff;               // block offsets as 32-bit integers
   // Slots. A batch is a run of proton cores; it owns the slot rows [core][x][neutron parity][position
   // of u][target neutron]. zoff: first slot row of (core, x, neutron parity) inside its batch.

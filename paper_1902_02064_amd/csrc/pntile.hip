@@ -45,8 +45,11 @@ struct PNTileArgs {
   int c0, cval, lr, cpr, cprv;
   int ns;
   int64_t vrow;  // bytes per row of V
-  const int* rkp;  // [core * ns + state]: position << 24 | local index of core + state, -1 inside
-  const int* rkn;
+  // [core * ns + state]: position << 24 | local index of core + state, -1 inside; of the species whose core an item
+  // fixes and of the species whose cores it runs over
+  const int* rkf;
+  const int* rkr;
+  int swap;           // the neutron core is fixed
   const int* blk_off;  // block offsets (the tables are used only while D < 2^31)
   const int* blk_dn;
   const int* pr_off;
@@ -55,9 +58,9 @@ struct PNTileArgs {
   const T* hb;
   const int* rect;    // per rectangle: pair block, first entry of its list in rblk
   const int* rblk;    // per rectangle and pair: target block << 1 | parity of its neutron sector, -1 if none
-  const int* zoff;    // [(core * ns + x) * 2 + neutron parity]: first slot row in the batch
-  int zstep;          // slot rows between positions of u (0: the neutron states of the target's sector)
-  const int4* items;  // per work item: rectangle, proton core, first neutron core, count
+  const int* zoff;    // several batches: [(core * ns + x) * 2 + neutron parity], first slot row in the batch
+  int zstep;          // one batch: slot rows between positions of u (0: the neutron states of the target's sector)
+  const int4* items;  // per work item: rectangle, fixed core, first core of the run, count
   int nitems, spread;  // spread: taken in order by all XCDs, else a contiguous range for each
   unsigned vbytes, zbytes;  // of V (where it stays below 4 GiB) and of a slot buffer
   // the previous batch, added to W by the first nred workgroups
@@ -135,20 +138,21 @@ __global__ __launch_bounds__(256) void pn_sum_kernel(PNTileArgs<T> a, int rows, 
   }
 }
 
-// Per-item tables in LDS: the pair states that the proton core allows, in order (neutron state u,
-// first V row of proton row K_p + x, first slot row of the core and x, position of x in the
-// target's proton word, slot rows between positions of u, index in the pair block).
+// Per-item tables in LDS: the pair states that the fixed core allows, in order. Below, `state` is the m-state of
+// the run's species and `loc` the index of core + state in its sector: V row row + mul * loc, slot row
+// z + step * (position of state) + mul * loc; pos: position of the fixed species' state; id: index in the pair block.
 struct PairList {
-  int u[PN_MAXPAIR], row[PN_MAXPAIR], z[PN_MAXPAIR], pos[PN_MAXPAIR], step[PN_MAXPAIR], id[PN_MAXPAIR];
+  int state[PN_MAXPAIR], row[PN_MAXPAIR], mul[PN_MAXPAIR], z[PN_MAXPAIR], pos[PN_MAXPAIR], step[PN_MAXPAIR],
+      id[PN_MAXPAIR];
 };
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// The core pairs of one item whose proton core allows d <= 4 KS pair states. The block is the same for
-// every neutron core, so the 16 columns of a matrix instruction are shared by KN of them: lane c
-// serves neutron core c / lr and VPL adjacent columns (one load or store of up to 16 bytes), and VPL
-// instructions take a lane's columns one after the other. A wavefront lists KN neutron cores at a
+// The core pairs of one item whose fixed core allows d <= 4 KS pair states. The block is the same for
+// every core of the run, so the 16 columns of a matrix instruction are shared by KN of them: lane c
+// serves core c / lr and VPL adjacent columns (one load or store of up to 16 bytes), and VPL
+// instructions take a lane's columns one after the other. A wavefront lists KN cores at a
 // time, a lane per pair state (V offset and slot offset, halved, with the sign on top; NO_ROW where the
-// neutron core holds u), runs the KS k-steps of each 16-target tile over the block's fragments, and
+// core holds the state), runs the KS k-steps of each 16-target tile over the block's fragments, and
 // during the last tile gathers each k-step's source rows of the next KN cores into the registers that
 // the step has just used.
 template <class T, int VPL, int KN, bool BIG, int KS>
@@ -162,9 +166,9 @@ struct CorePairs {
   const T* Af;
   unsigned* L;  // this wavefront's lists: [stage][V offsets, slot offsets][LW]
   int first, count;
-  int l, c, kq, q, pu;
+  int l, c, kq, q, pst;
   bool have;
-  unsigned vrow, vh, rh, prow, pz, pstep, psg, cb, sb, at0;
+  unsigned vrow, vmul, zmul, prow, pz, pstep, psg, cb, sb, at0;
   __amdgpu_buffer_rsrc_t vs, zs;
   int en[NO];
 
@@ -177,11 +181,12 @@ struct CorePairs {
     const int i = min(l % LP, d - 1);
     have = l % LP < d;
     vrow = (unsigned)a.vrow;
-    vh = vrow >> 1;
-    rh = (unsigned)(a.lr * VPL * (int)sizeof(T)) >> 1;
-    pu = P.u[i];
+    const unsigned vh = vrow >> 1, rh = (unsigned)(a.lr * VPL * (int)sizeof(T)) >> 1, mul = (unsigned)P.mul[i];
+    pst = P.state[i];
     prow = BIG ? (unsigned)P.row[i] : (unsigned)P.row[i] * vh;
+    vmul = BIG ? mul : mul * vh;
     pz = (unsigned)P.z[i] * rh;
+    zmul = mul * rh;
     pstep = (unsigned)P.step[i] * rh;
     psg = (unsigned)P.pos[i];
     q = min(c / a.lr, KN - 1);  // lanes beyond KN * lr repeat the last core
@@ -194,12 +199,12 @@ struct CorePairs {
     vs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.V + a.c0), (short)0, (int)a.vbytes, 0x00020000);
     zs = __builtin_amdgcn_make_buffer_rsrc((void*)a.Z, (short)0, (int)a.zbytes, 0x00020000);
   }
-  // neutron-core table entries of the KN cores from n on
+  // table entries of the KN cores from n on
   __device__ __forceinline__ void entries(int n) {
 #pragma unroll
     for (int o = 0; o < NO; o++) {
       const int core = n + o * PPO + l / LP;
-      en[o] = core < count && o * PPO + l / LP < KN ? a.rkn[(first + core) * a.ns + pu] : -1;
+      en[o] = core < count && o * PPO + l / LP < KN ? a.rkr[(first + core) * a.ns + pst] : -1;
     }
   }
   // lists the KN cores whose entries are held, then fetches the entries from `next` on
@@ -211,8 +216,8 @@ struct CorePairs {
       const bool ok = have && rn >= 0;
       const unsigned loc = (unsigned)rn & 0xFFFFFFu, pos = (unsigned)rn >> 24;
       const unsigned sg = (psg + pos) << 31;
-      Rv[o * 64 + l] = ok ? (BIG ? prow + loc : prow + __umul24(loc, vh)) | sg : BIG ? ~0u : NO_ROW >> 1;
-      Rv[LW + o * 64 + l] = ok ? (pz + pos * pstep + __umul24(loc, rh)) | sg : NO_ROW >> 1;
+      Rv[o * 64 + l] = ok ? (prow + __umul24(loc, vmul)) | sg : BIG ? ~0u : NO_ROW >> 1;
+      Rv[LW + o * 64 + l] = ok ? (pz + pos * pstep + __umul24(loc, zmul)) | sg : NO_ROW >> 1;
     }
     entries(next);
     // the lists are written and read by this wavefront only: LDS operations of one wavefront
@@ -290,10 +295,10 @@ struct CorePairs {
 };
 #endif
 
-// One work item: a proton core K_p and a run of neutron cores of one (2M, parity) group. The pair
-// states that K_p leaves free are listed once, and the block of H_M over them is laid out as the
-// matrix instructions read it (one conflict-free LDS read per fragment). The neutron cores then
-// only mask sources and targets: their blocked pairs read zeros and write nothing. The first
+// One work item: a proton core K_p and a run of neutron cores of one (2M, parity) group, or a neutron core and
+// a run of proton cores. The pair states that the fixed core leaves free are listed once, and the block of H_M
+// over them is laid out as the matrix instructions read it (one conflict-free LDS read per fragment). The cores
+// of the run then only mask sources and targets: their blocked pairs read zeros and write nothing. The first
 // workgroups of a launch add the previous batch.
 template <class T, int VPL, int KN, bool BIG>
 __global__ __launch_bounds__(256, 4) void pn_tile_kernel(PNTileArgs<T> a) {
@@ -314,21 +319,27 @@ __global__ __launch_bounds__(256, 4) void pn_tile_kernel(PNTileArgs<T> a) {
   const int q0 = a.pr_off[k], D2 = a.pr_off[k + 1] - q0;
   const T* hg = a.hb + a.hb_off[k];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int xu = a.pr_xu[q0 + min(l, D2 - 1)], x = xu & 255;
+  const int xu = a.pr_xu[q0 + min(l, D2 - 1)], fst = a.swap ? xu >> 8 : xu & 255;
   const int tb = a.rblk[rb0 + min(l, D2 - 1)];
-  const int rp = a.rkp[it.y * a.ns + x];
-  const bool lok = l < D2 && tb >= 0 && rp >= 0;
+  const int rf = a.rkf[it.y * a.ns + fst];
+  const bool lok = l < D2 && tb >= 0 && rf >= 0;
   const uint64_t mask = __ballot(lok);
   const int d = __popcll(mask);
   if (d == 0) return;  // the same for every wavefront
   if (w == 0 && lok) {
     const int i = __popcll(mask & ((1ull << l) - 1));
-    const int dn = a.blk_dn[tb >> 1];
-    P.u[i] = xu >> 8;
-    P.row[i] = a.blk_off[tb >> 1] + (rp & 0xFFFFFF) * dn;
-    P.z[i] = a.zoff[(it.y * a.ns + x) * 2 + (tb & 1)];
-    P.pos[i] = rp >> 24;
-    P.step[i] = a.zstep ? a.zstep : dn;
+    const int dn = a.blk_dn[tb >> 1], row = a.blk_off[tb >> 1] + (rf & 0xFFFFFF) * (a.swap ? 1 : dn), pos = rf >> 24;
+    P.state[i] = a.swap ? xu & 255 : xu >> 8;
+    P.row[i] = row;
+    P.mul[i] = a.swap ? dn : 1;
+    P.pos[i] = pos;
+    if (a.zstep) {  // one batch: [position of x][position of u][target]
+      P.z[i] = pos * (a.swap ? a.zstep : a.nneut * a.zstep) + row;
+      P.step[i] = a.swap ? a.nneut * a.zstep : a.zstep;
+    } else {
+      P.z[i] = a.zoff[(it.y * a.ns + fst) * 2 + (tb & 1)];
+      P.step[i] = dn;
+    }
     P.id[i] = l;
   }
   __syncthreads();
@@ -549,17 +560,41 @@ void build_pn_tiles(Model& m) {
   const int nbat = (int)bat0.size() - 1;
   // one batch: the slots of all targets lie one position pair after the other, [x][u][target]
   T.zstep = nbat == 1 ? (int)m.dim : 0;
-  // Work items of a batch: per run of proton cores of one group, per neutron group with a rectangle, up
-  // to `chunk` neutron cores at a time (TRBL_PN_CHUNK: a tuning override) for each core of the run. Items go
-  // to the XCDs in contiguous ranges. One batch: 256 neutron cores, and runs of 16 consecutive (colex)
-  // cores, so that the items in flight on an XCD share source rows in its L2. Several: 64 and one core
-  // after the other, so that a batch has enough items for the chip (pf 6+6: 645 against 696 ms).
+  // Work items: per fixed core, the cores of one group of the other species that make a rectangle with it, up to
+  // `chunk` at a time. An item's set-up, and the lanes of a matrix instruction that the cores share, pay for
+  // runs of some cores, so with one batch the items run over the protons where they would hold fewer than 4
+  // neutron cores on average and the proton runs are longer (ms, over neutrons / protons, FP64 8 and 32 columns: pf
+  // 4+2 0.148 / 0.100, 0.408 / 0.305; pf 5+1 0.175 / 0.129, 0.280 / 0.210; pf 3+2 0.068 / 0.063, 0.141 / 0.132; the
+  // other way round pf 2+4 0.106 / 0.169, 0.288 / 0.391). TRBL_PN_RUN=p or n: a testing override.
+  auto count_items = [&](bool sw, int ch) {
+    int64_t n = 0;
+    for (size_t ip = 0; ip < groups[0].size(); ip++)
+      for (size_t in = 0; in < groups[1].size(); in++)
+        if (rect_of[ip * groups[1].size() + in] >= 0) {
+          const int np = groups[0][ip].count, nn = groups[1][in].count;
+          n += (int64_t)(sw ? nn : np) * (((sw ? np : nn) + ch - 1) / ch);
+        }
+    return n;
+  };
+  T.swap = nbat == 1 && count_items(false, 1) < 4 * count_items(false, PN_TPB) &&
+           count_items(true, PN_TPB) < count_items(false, PN_TPB);
+  if (const char* ev = std::getenv("TRBL_PN_RUN")) T.swap = ev[0] == 'p' && nbat == 1;
+  // One batch: as many as 256 cores an item while that makes 768 items, three for a CU, else fewer, down to 8 (two
+  // cores a wavefront; FP64 8 and 32 columns, 256 / 8 cores: pf 1+4 0.107 / 0.068, 0.272 / 0.113; pf 1+5 0.254 /
+  // 0.189, 0.495 / 0.233; with 32 cores pf 2+4 0.126 / 0.106, 0.358 / 0.288). The fixed cores of a group go in runs of 16
+  // consecutive (colex) ones, one chunk after the other, so that the items in flight on an XCD, which
+  // takes a contiguous range of them, share source rows in its L2. Several batches: 64 cores and
+  // one fixed core after the other, so that a batch has enough items for the chip (pf 6+6: 645 against 696 ms).
+  // TRBL_PN_CHUNK: a tuning override.
   int chunk = nbat == 1 ? PN_TPB : 64;
+  while (nbat == 1 && chunk > 8 && count_items(T.swap, chunk) < 768) chunk /= 2;
   if (const char* ev = std::getenv("TRBL_PN_CHUNK")) chunk = std::max(8, std::min(PN_TPB, std::atoi(ev)));
   const int core_run = nbat == 1 ? 16 : 1;
-  std::vector<int> group_of(nc0);
-  for (int g = 0; g < (int)groups[0].size(); g++)
-    for (int cp = groups[0][g].start; cp < groups[0][g].start + groups[0][g].count; cp++) group_of[cp] = g;
+  const std::vector<Group>&gf = groups[T.swap ? 1 : 0], &gr = groups[T.swap ? 0 : 1];
+  const int nfix = (int)cw[T.swap ? 1 : 0].size();
+  std::vector<int> group_of(nfix);
+  for (int g = 0; g < (int)gf.size(); g++)
+    for (int c = gf[g].start; c < gf[g].start + gf[g].count; c++) group_of[c] = g;
   std::vector<int64_t> blk_row0(m.blocks.size() + 1, 0);
   for (size_t b = 0; b < m.blocks.size(); b++) blk_row0[b + 1] = blk_row0[b] + m.blocks[b].dp;
   TRBL_REQUIRE(blk_row0.back() < ((int64_t)1 << 31), TRBL_E_INVALID, "too many proton rows");
@@ -570,16 +605,15 @@ void build_pn_tiles(Model& m) {
     PNTiles::Batch B{};
     B.item0 = (int)(items.size() / 4);
     B.row0 = (int)trow.size();
-    for (int t0 = bat0[ib]; t0 < bat0[ib + 1];) {
+    for (int t0 = bat0[ib], te = nbat == 1 ? nfix : bat0[ib + 1]; t0 < te;) {
       const int g = group_of[t0];
-      const int t1 = std::min(std::min(bat0[ib + 1], groups[0][g].start + groups[0][g].count), t0 + core_run);
-      for (int in = 0; in < ngn; in++) {
-        const int r = rect_of[g * ngn + in];
+      const int t1 = std::min(std::min(te, gf[g].start + gf[g].count), t0 + core_run);
+      for (int ir = 0; ir < (int)gr.size(); ir++) {
+        const int r = T.swap ? rect_of[ir * ngn + g] : rect_of[g * ngn + ir];
         if (r < 0) continue;
-        const Group& gn = groups[1][in];
-        for (int c0 = 0; c0 < gn.count; c0 += chunk)
-          for (int cp = t0; cp < t1; cp++)
-            items.insert(items.end(), {r, cp, gn.start + c0, std::min(chunk, gn.count - c0)});
+        for (int c0 = 0; c0 < gr[ir].count; c0 += chunk)
+          for (int cf = t0; cf < t1; cf++)
+            items.insert(items.end(), {r, cf, gr[ir].start + c0, std::min(chunk, gr[ir].count - c0)});
       }
       t0 = t1;
     }
@@ -598,27 +632,27 @@ void build_pn_tiles(Model& m) {
       for (size_t i = 0; i < by_cost.size(); i++)
         for (int q = 0; q < 4; q++) items[4 * ((size_t)B.item0 + i) + q] = by_cost[i].second[q];
     }
-    // slot rows and target rows of the batch
-    std::map<int64_t, std::vector<int>> to;  // target row (block row0 + proton row) -> first slot rows
-    int64_t at = 0;
-    for (int cp = bat0[ib]; cp < bat0[ib + 1]; cp++)
-      for (int x = 0; x < ns; x++)
-        for (int q = 0; q < 2; q++) {
-          int& z = zoff[((size_t)cp * ns + x) * 2 + q];
-          if (z < 0) continue;
-          const int b = z;
-          const int r = rk[0][(size_t)cp * ns + x], pl = r & 0xFFFFFF, dn = m.blocks[b].dn;
-          z = (int)(T.zstep ? (int64_t)(r >> 24) * m.n_neut * m.dim + m.blocks[b].off + (int64_t)pl * dn : at);
-          if (nbat > 1) to[blk_row0[b] + pl].push_back(z);
-          at += (int64_t)m.n_neut * dn;
-        }
-    size_t b = 0;
-    for (auto& kv : to) {
-      while (kv.first >= blk_row0[b + 1]) b++;
-      const int dn = m.blocks[b].dn;
-      trow.push_back({m.blocks[b].off + (kv.first - blk_row0[b]) * dn, dn, (int)tent.size(), (int)kv.second.size(), 0});
-      tent.insert(tent.end(), kv.second.begin(), kv.second.end());
-      B.maxdn = std::max(B.maxdn, dn);
+    if (nbat > 1) {  // slot rows and target rows of the batch
+      std::map<int64_t, std::vector<int>> to;  // target row (block row0 + proton row) -> first slot rows
+      int64_t at = 0;
+      for (int cp = bat0[ib]; cp < bat0[ib + 1]; cp++)
+        for (int x = 0; x < ns; x++)
+          for (int q = 0; q < 2; q++) {
+            int& z = zoff[((size_t)cp * ns + x) * 2 + q];
+            if (z < 0) continue;
+            const int b = z, pl = rk[0][(size_t)cp * ns + x] & 0xFFFFFF;
+            z = (int)at;
+            to[blk_row0[b] + pl].push_back(z);
+            at += (int64_t)m.n_neut * m.blocks[b].dn;
+          }
+      size_t b = 0;
+      for (auto& kv : to) {
+        while (kv.first >= blk_row0[b + 1]) b++;
+        const int dn = m.blocks[b].dn;
+        trow.push_back({m.blocks[b].off + (kv.first - blk_row0[b]) * dn, dn, (int)tent.size(), (int)kv.second.size(), 0});
+        tent.insert(tent.end(), kv.second.begin(), kv.second.end());
+        B.maxdn = std::max(B.maxdn, dn);
+      }
     }
     B.nitems = (int)(items.size() / 4) - B.item0;
     B.nrows = (int)trow.size() - B.row0;
@@ -715,8 +749,9 @@ void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int6
   a.ns = m.ns;
   a.nneut = m.n_neut;
   a.vrow = ldv * (int64_t)sizeof(T);
-  a.rkp = P.rk[0].as<int>();
-  a.rkn = P.rk[1].as<int>();
+  a.swap = P.swap;
+  a.rkf = P.rk[P.swap ? 1 : 0].as<int>();
+  a.rkr = P.rk[P.swap ? 0 : 1].as<int>();
   a.blk_off = P.boff.as<int>();
   a.blk_dn = m.dt.blk_dn.as<int>();
   a.pr_off = P.pr_off.as<int>();
@@ -729,7 +764,9 @@ void launch_pn_tiles(const Model& m, int nb, const T* V, int64_t ldv, T* W, int6
   a.zstep = P.zstep;
   a.spread = P.batches.size() > 1;
   a.tent = P.tent.as<int>();
-  const bool big = (double)m.dim * (double)a.vrow > (double)NO_ROW || a.vrow >= (1 << 25);
+  // (row steps between states of the run are multiplied in 24 bits)
+  const bool big = (double)m.dim * (double)a.vrow > (double)NO_ROW ||
+                   (double)a.vrow * (P.swap ? m.max_dn : 1) >= (double)(1 << 25);
   for (int c0 = 0; c0 < nb; c0 += WIDE) {
     a.c0 = c0;
     a.cval = std::min(WIDE, nb - c0);

@@ -13,9 +13,11 @@ pytestmark = pytest.mark.gpu
 
 MIXED_PAR = ((0, 1, 1), (0, 2, 5), (0, 1, 3))  # both parities in one proton row
 SPACES = {
+    "pf21": (PF_ORBITS, 2, 1, 1, 0),
     "pf41": (PF_ORBITS, 4, 1, 1, 0),
     "pf14": (PF_ORBITS, 1, 4, 1, 0),
     "pf32": (PF_ORBITS, 3, 2, 1, 0),
+    "pf22": (PF_ORBITS, 2, 2, 0, 0),
     "sd61": (SD_ORBITS, 6, 1, 1, 0),
     "mixpar31": (MIXED_PAR, 3, 1, 0, 0),
     "mixpar13": (MIXED_PAR, 1, 3, 0, 0),
@@ -61,3 +63,29 @@ def _check(space, env):
 @pytest.mark.parametrize("space", SPACES)
 def test_short_rows_match_oracle(space):
     _check(space, {"TRBL_PN_TILES": "2"})
+
+
+@pytest.mark.parametrize("run", ["p", "n"])
+@pytest.mark.parametrize("space", SPACES)
+def test_runs_over_either_species(space, run):
+    """Work items that run over proton or over neutron cores, whichever the space would take."""
+    _check(space, {"TRBL_PN_TILES": "2", "TRBL_PN_RUN": run})
+
+
+def test_runs_over_protons_beyond_24_bit_row_steps():
+    """Columns of a block with 8 MiB rows: the rows of consecutive proton states, up to 4 rows apart, are 2^25 bytes
+    away (64-bit row addresses), while the whole block stays below 4 GiB. The same columns packed give the same
+    products; their sums over D products differ by at most gamma_D of sum |x| |H x| each."""
+    g, _ = _model("pf21", {"TRBL_PN_TILES": "2", "TRBL_PN_RUN": "p"}, oracle=False)
+    ld = 1 << 20
+    assert 8 * ld * g.dim < (1 << 32) - (1 << 16)
+    X = torch.zeros((g.dim, ld), dtype=torch.float64, device="cuda")
+    cols = [0, 1, ld // 2, ld - 1]
+    V = torch.from_numpy(random_block(3, g.dim, len(cols))).cuda()
+    X[:, cols] = V
+    say("expect on", tuple(X.shape))
+    got = g.expect(X)
+    ref, HV = g.expect(V), g.apply(V)
+    u = 2.0 ** -53
+    bound = 2 * g.dim * u / (1 - g.dim * u) * (V.abs() * HV.abs()).sum(0).cpu().numpy()
+    assert np.all(np.abs(got[cols] - ref) <= bound)
