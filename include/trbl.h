@@ -149,7 +149,7 @@ int trbl_random_tbme(const trbl_orbit* orbits, int n_orbits, uint64_t seed, doub
    tbme: n_v host elements. Copies everything, builds the one-body jump and
    identical-particle tables of App. B on the device. For single-species spaces whose slots fit
    in a quarter of the free device memory, and for two species where a core pair carries enough
-   source pairs (pf-shell spaces, sd shell up to 4+4), it also builds the core-pair blocks of the
+   source pairs (pf-shell spaces from 2,500 states on, some of the sd shell), it also builds the core-pair blocks of the
    matrix-core products and their slot buffers, which the model keeps: for two species
    n_prot * n_neut * D * 128 bytes where that is below 4 GiB and a quarter of the free memory,
    else two buffers of 512 MiB, and C(n, 2) * D * 8 doubles for n nucleons of one species. Setting

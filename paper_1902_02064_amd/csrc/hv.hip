@@ -206,7 +206,9 @@ static void run_hv(const Model& m, int nb, const void* V, int64_t ldv, void* W, 
   a.citem0 = P.citem0.as<int64_t>();
   // with the pair-block tables the rows and columns kernels write the identical-particle parts and
   // the pair blocks add the pn part
-  const bool own = m.pn.on && !(m.pn.one_tile && nb * sizeof(T) > 128) && ldv * (int64_t)sizeof(T) < ((int64_t)1 << 32);
+  const size_t row = nb * sizeof(T);
+  const bool own = m.pn.on && !(m.pn.one_tile && (row <= (size_t)m.pn.min_row || row > 128)) &&
+                   ldv * (int64_t)sizeof(T) < ((int64_t)1 << 32);
   a.own = own ? 1 : 0;
   if (!own) {
     dispatch_hv<T>(a, P, s, 3, ~0u);

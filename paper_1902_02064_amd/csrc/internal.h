@@ -184,7 +184,8 @@ struct HVPlan {
 struct PNTiles {
   bool on = false;
   bool force = false;        // in every space that allows them (TRBL_PN_TILES=2)
-  bool one_tile = false;     // only for products of one column tile (128-byte rows)
+  bool one_tile = false;     // only for products of one column tile, rows of more than min_row to 128 bytes
+  int min_row = 0;
   bool swap = false;         // items fix a neutron core and run over proton cores
   int max_pairs = 0;         // widest pair block
   DevBuf rk[2];              // [core * ns + state]: position of state << 24 | local index of core + state, -1 inside

@@ -390,17 +390,24 @@ void build_pn_tiles(Model& m) {
   int maxp = 0;
   for (auto& v : pairs) maxp = std::max(maxp, (int)v.size());
   if (maxp > PN_MAXPAIR) return;
-  // Where the pair blocks are built (ms per product, jump lists / pair blocks; TRBL_PN_TILES=2 builds them
-  // regardless). A slot row, written and read back, carries the products of one core pair: on average
-  // about L = (pair-weighted mean block size) x (share of the proton states outside a proton core) x (the
-  // same for neutrons) source pairs. From L = 11 on (all pf spaces, sd up to 4+4; FP64 at 1, 8, 16 columns):
-  // pf 4+4 (L = 31) 1.85 / 0.93, 3.10 / 1.70, 5.49 / 3.24; pf 3+3 0.189 / 0.085, 0.276 / 0.122, 0.355 /
-  // 0.177; sd 4+4 (11.4) 0.065 / 0.057, 0.080 / 0.062, 0.113 / 0.086; sd 4+5 (10.1) 0.087 / 0.061, 0.089 /
-  // 0.085, 0.131 / 0.134; sd 6+6 (6.9) 0.087 / 0.111, 0.130 / 0.186, 0.180 / 0.285. Below L = 16 products
-  // of more than one column tile keep the jump lists (sd 4+4, FP64, 32 columns: 0.130 / 0.171).
-  // Below 2,500 states the launches decide (sd 2+2, D = 640, 4 columns: 0.041 / 0.052; pf 3+1, D = 2,550:
-  // 0.074 / 0.058), and with one proton the jump lists stage each source row for few targets
-  // (pf 1+4, 8 columns: 0.092 / 0.107; pf 4+1: 0.322 / 0.063).
+  // Where the pair blocks are built and taken (ms per product, jump lists / pair blocks; TRBL_PN_TILES=2 takes them
+  // regardless). A slot row, written and read back, carries the products of one core pair: on average about
+  // L = (pair-weighted mean block size) x (share of the proton states outside a proton core) x (the same for
+  // neutrons) source pairs. A product on pair blocks costs at least about 0.06 ms of launches.
+  // L >= 16 (pf spaces): from 2,500 states on, FP64 at 1, 8, 16, 32 columns: pf 4+4 (L = 31) 1.85 / 0.90, 3.18 / 1.62,
+  // 5.56 / 3.25, 11.4 / 7.2; pf 3+3 0.184 / 0.083, 0.259 / 0.122, 0.356 / 0.178, 0.547 / 0.388; pf 1+4 0.062 / 0.066,
+  // 0.092 / 0.074, 0.127 / 0.090, 0.146 / 0.112; pf 3+1 (D = 2,550) 0.062 / 0.059, 0.069 / 0.064, 0.079 / 0.068,
+  // 0.160 / 0.082; pf 2+1 (D = 472) 0.036 / 0.062, 0.039 / 0.064, 0.045 / 0.063, 0.048 / 0.078. Below 5,000 states
+  // with no more protons than neutrons only rows of 65 to 128 bytes, where the jump lists stage ragged widths without
+  // the DMA (8, 12, 16, 32 columns: pf 1+3 0.042 / 0.062, 0.090 / 0.065, 0.072 / 0.068, 0.072 / 0.082; pf 2+2 0.047 /
+  // 0.060, 0.062 / 0.060, 0.056 / 0.061, 0.059 / 0.077).
+  // L from 11 to 16 (sd): the same rows (8, 12, 16, 32 columns: sd 4+4 (L = 11.4) 0.051 / 0.065, 0.117 / 0.079, 0.106 /
+  // 0.084, 0.110 / 0.160; sd 2+5 0.032 / 0.063, 0.093 / 0.065, 0.072 / 0.067, 0.073 / 0.079), but not where the jump
+  // lists can share a row between four parts of a workgroup (sectors of up to 90 neutron states, up to 256 proton
+  // rows: sd 3+4 0.037 / 0.062, 0.055 / 0.068, 0.049 / 0.069, 0.088 / 0.098), and from 33 bytes on where there are
+  // more than 512 proton rows, which they share between two (sd 5+3, FP32, 9 columns: 0.080 / 0.066).
+  // L < 11: never (sd 4+5 (10.1) 0.057 / 0.085, 0.169 / 0.127, 0.131 / 0.136, 0.152 / 0.238; sd 6+6 (6.9) 0.125 /
+  // 0.178, 0.210 / 0.286, 0.179 / 0.288, 0.332 / 0.574).
   {
     double n1 = 0.0, n2 = 0.0;
     for (auto& v : pairs) {
@@ -408,8 +415,10 @@ void build_pn_tiles(Model& m) {
       n2 += (double)v.size() * (double)v.size();
     }
     const double L = n2 / n1 * (double)(ns - (m.n_prot - 1)) / ns * (double)(ns - (m.n_neut - 1)) / ns;
-    if ((L < 11.0 || m.dim < 2500 || m.n_prot == 1) && !T.force) return;
-    T.one_tile = L < 16.0 && !T.force;
+    const bool split = m.max_dn <= 90 && m.np_total <= 256;
+    if ((m.dim < 2500 || L < (split ? 16.0 : 11.0)) && !T.force) return;
+    T.one_tile = !T.force && (L < 16.0 || (m.dim < 5000 && m.n_prot <= m.n_neut));
+    T.min_row = m.np_total > 512 ? 32 : 64;
   }
   std::vector<int> pr_off(nk + 1, 0), pr_xu, hb_off(nk + 1, 0);
   for (int k = 0; k < nk; k++) {
