@@ -105,9 +105,10 @@ static HVPlan& plan_for(const Model& m, int nb, size_t elt) {
     B.maxdn = maxdn;
     B.items = i0.back();
     // A row's jump groups are shared by 2, 4 or 8 parts of a workgroup where all workgroups stay resident at
-    // once: 16 KB of LDS a part, about 4096 wavefronts on 256 CUs. us per product, one part / split: sd 2+2 nb 4
-    // 40.1 / 18.6 (8), sd 3+4 nb 8 65.6 / 52.5 (4; 57.5 with 8), sd 4+5 nb 8 89.4 / 56.8 (4), sd 4+4 nb 32
-    // 127.6 / 109.3 (2); beyond, sd 6+6 nb 8 (2,772 wavefronts): 126.4 / 145.9 (2).
+    // once: 16 KB of LDS a part, 512 threads a workgroup, about 4096 wavefronts on 256 CUs. us per product, one
+    // part / split: sd 2+2 nb 4 40.1 / 18.6 (8), sd 3+3 nb 8 58.9 / 27.5 (8; 33.8 with 4), pf 2+2 nb 4 68.4 / 30.9 (8;
+    // 43.5 with 4), sd 3+4 nb 8 65.6 / 36.7 (4: sectors of more than 64 states), sd 4+5 nb 8 89.4 / 56.8 (4), sd 4+4
+    // nb 32 127.6 / 109.3 (2); beyond, sd 6+6 nb 8 (2,772 wavefronts): 126.4 / 145.9 (2).
     // TRBL_HV_SPLIT: the most parts (tuning override).
     const bool tiny = B.ntb == 256 && (m.max_dn + zrows(C)) * C * elt <= ROW_TINY;
     // two buffers of 12 KB take the LDS of one of 24 KB and hide the copies (sd 6+6: 126.4 -> 124.7 us)
@@ -117,7 +118,7 @@ static HVPlan& plan_for(const Model& m, int nb, size_t elt) {
       const int most = env ? std::atoi(env) : 8;
       const int64_t waves = B.items * (B.nthr / 64);
       for (int sp : {8, 4, 2})
-        if (B.split == 1 && sp <= most && B.nthr * sp <= 512 && B.items <= (sp == 8 ? 128 : 256 * (160 / (16 * sp + 1))) &&
+        if (B.split == 1 && sp <= most && B.nthr * sp <= 512 && B.items <= 256 * (160 / (16 * sp + 1)) &&
             waves * sp <= 4096)
           B.split = sp;
     }

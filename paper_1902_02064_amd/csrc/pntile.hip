@@ -397,10 +397,11 @@ void build_pn_tiles(Model& m) {
   // L >= 16 (pf spaces): from 2,500 states on, FP64 at 1, 8, 16, 32 columns: pf 4+4 (L = 31) 1.85 / 0.90, 3.18 / 1.62,
   // 5.56 / 3.25, 11.4 / 7.2; pf 3+3 0.184 / 0.083, 0.259 / 0.122, 0.356 / 0.178, 0.547 / 0.388; pf 1+4 0.062 / 0.066,
   // 0.092 / 0.074, 0.127 / 0.090, 0.146 / 0.112; pf 3+1 (D = 2,550) 0.062 / 0.059, 0.069 / 0.064, 0.079 / 0.068,
-  // 0.160 / 0.082; pf 2+1 (D = 472) 0.036 / 0.062, 0.039 / 0.064, 0.045 / 0.063, 0.048 / 0.078. Below 5,000 states
-  // with no more protons than neutrons only rows of 65 to 128 bytes, where the jump lists stage ragged widths without
-  // the DMA (8, 12, 16, 32 columns: pf 1+3 0.042 / 0.062, 0.090 / 0.065, 0.072 / 0.068, 0.072 / 0.082; pf 2+2 0.047 /
-  // 0.060, 0.062 / 0.060, 0.056 / 0.061, 0.059 / 0.077).
+  // 0.160 / 0.082; pf 2+1 (D = 472) 0.028 / 0.062, 0.031 / 0.064, 0.037 / 0.063, 0.048 / 0.078. Below 5,000 states
+  // spaces of several protons keep the jump lists where these share a row as below (8, 12, 16, 32 columns: pf 2+2
+  // 0.034 / 0.060, 0.047 / 0.060, 0.043 / 0.061, 0.059 / 0.077), and with one proton, where twenty rows leave the chip
+  // empty, the pair blocks take rows of 65 to 128 bytes (pf 1+3 0.042 / 0.062, 0.090 / 0.065, 0.072 / 0.068, 0.072 /
+  // 0.082).
   // L from 11 to 16 (sd): the same rows (8, 12, 16, 32 columns: sd 4+4 (L = 11.4) 0.051 / 0.065, 0.117 / 0.079, 0.106 /
   // 0.084, 0.110 / 0.160; sd 2+5 0.032 / 0.063, 0.093 / 0.065, 0.072 / 0.067, 0.073 / 0.079), but not where the jump
   // lists can share a row between four parts of a workgroup (sectors of up to 90 neutron states, up to 256 proton
@@ -415,9 +416,9 @@ void build_pn_tiles(Model& m) {
       n2 += (double)v.size() * (double)v.size();
     }
     const double L = n2 / n1 * (double)(ns - (m.n_prot - 1)) / ns * (double)(ns - (m.n_neut - 1)) / ns;
-    const bool split = m.max_dn <= 90 && m.np_total <= 256;
-    if ((m.dim < 2500 || L < (split ? 16.0 : 11.0)) && !T.force) return;
-    T.one_tile = !T.force && (L < 16.0 || (m.dim < 5000 && m.n_prot <= m.n_neut));
+    const bool split = m.n_prot > 1 && m.max_dn <= 90 && m.np_total <= 256;
+    if ((m.dim < 2500 || L < 11.0 || ((L < 16.0 || m.dim < 5000) && split)) && !T.force) return;
+    T.one_tile = !T.force && (L < 16.0 || (m.dim < 5000 && m.n_prot == 1));
     T.min_row = m.np_total > 512 ? 32 : 64;
   }
   std::vector<int> pr_off(nk + 1, 0), pr_xu, hb_off(nk + 1, 0);
