@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256) void apply_small_kernel(const TI* Bin, int64_t
 
 // The same as chol_kernel below for nb <= 16, one element (i, j) of the matrix a thread, and for nb <= 8 with
 // the sum of the partials in the same launch, 16 or 64 threads an element. A step of the elimination (kept as
-// a_ij - a_ki a_kj / a_kk, the roots taken at the end) costs one barrier, against three in LDS. nb = 8, 256
+// a_ij - a_ki (a_kj / a_kk), the roots taken at the end) costs one barrier, against three in LDS. nb = 8, 256
 // partials: 10 us, 13 us as a sum and a factorisation in LDS.
 __global__ __launch_bounds__(1024) void chol_small_kernel(const double* __restrict__ part, int G, int nb, double* R,
                                                           double* Rinv, const double* Rprev, double* beta,
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(1024) void chol_small_kernel(const double* __restri
       if (j == k) rd[k] = 1.0 / sqrt(p);
       A[k * 17 + j] = j < k ? 0.0 : j == k ? sqrt(p) : s / sqrt(p);
     }
-    if (mine && i > k && j >= i) s -= row[k & 1][i] * row[k & 1][j] / p;
+    if (mine && i > k && j >= i) s -= row[k & 1][i] * (row[k & 1][j] / p);  // (the product of two could overflow)
   }
   __syncthreads();
   // inverse of the upper-triangular R, one thread per column
