@@ -63,6 +63,7 @@ struct FlyCores {
   static constexpr int NO = KN > PPO ? KN / PPO : 1, DT = (KS + 3) / 4;
   static constexpr int LW = NO * 64;  // words of one list
   typedef typename Cols<T, VPL>::type cols;
+  typedef typename Cols<T, VPL>::stored stored;
   typedef Buf<(int)sizeof(cols)> B;
   const FlyTileArgs<T>& a;
   const T* Af;
@@ -188,7 +189,7 @@ struct FlyCores {
             for (int t = 0; t < VPL; t++) x[t] = (T)acc[t][v];
           }
           if (o != NO_ROW >> 1) {
-            cols* p = reinterpret_cast<cols*>(Zb + (uint64_t)z * rowb);
+            stored* p = reinterpret_cast<stored*>(Zb + (uint64_t)z * rowb);
             if constexpr (VPL > 1 && KN <= 4) __builtin_nontemporal_store(flipped(x, o), p);
             else *p = flipped(x, o);
           }

@@ -46,13 +46,16 @@ __device__ __forceinline__ float flip_if(float x, unsigned s) { return __int_as_
 
 // CT adjacent columns of one lane: CT column tiles interleave their columns (lane c of a 16-lane
 // group holds columns CT c .. CT c + CT - 1), so a lane's share of a row is one load or store.
+// In memory a lane's columns start at any column (`stored`): the last lane of a ragged row overlaps its neighbour.
 template <class T, int CT>
 struct Cols {
   typedef T type __attribute__((ext_vector_type(CT)));
+  typedef T stored __attribute__((ext_vector_type(CT), aligned(sizeof(T))));
 };
 template <class T>
 struct Cols<T, 1> {
   typedef T type;
+  typedef T stored;
 };
 
 // A byte offset beyond every V and slot offset: buffer loads return 0 there, stores write nothing.
