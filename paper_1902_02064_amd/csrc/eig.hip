@@ -23,7 +23,6 @@
 namespace trbl {
 
 constexpr int EIG_THREADS = 1024;
-constexpr int PNB = 8;         // Householder panel width
 
 __device__ static double block_sum(double v, double* red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

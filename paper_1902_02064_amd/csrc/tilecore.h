@@ -18,7 +18,6 @@ struct Mfma<double> {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int kq, int v) { return kq + 4 * v; }
-  static constexpr unsigned ZSHIFT = 7;  // bytes of a 16-value row: 128
 };
 template <>
 struct Mfma<float> {
@@ -27,7 +26,6 @@ struct Mfma<float> {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ int row(int kq, int v) { return 4 * kq + v; }
-  static constexpr unsigned ZSHIFT = 6;  // 64
 };
 
 constexpr int PN_TPB = 256;       // most core pairs of one work item
