@@ -208,8 +208,17 @@ static void run_hv(const Model& m, int nb, const void* V, int64_t ldv, void* W, 
   // with the pair-block tables the rows and columns kernels write the identical-particle parts and
   // the pair blocks add the pn part
   const size_t row = nb * sizeof(T);
-  const bool own = m.pn.on && !(m.pn.one_tile && (row <= (size_t)m.pn.min_row || row > 128)) &&
-                   ldv * (int64_t)sizeof(T) < ((int64_t)1 << 32);
+  bool own = m.pn.on && !(m.pn.one_tile && (row <= (size_t)m.pn.min_row || row > 128)) &&
+             ldv * (int64_t)sizeof(T) < ((int64_t)1 << 32);
+  // In spaces of several batches and more than 2,048 neutron states in a sector, narrow rows that the jump lists copy by
+  // DMA: their rows kernel then serves four targets a lane from one copy, while a slot row of the pair blocks costs
+  // its lists and stores at any width (ms, jump lists / pair blocks: pf 6+6 FP64 1, 2, 4, 8 columns 157 / 177, 151 / 192,
+  // 210 / 255, 455 / 372, FP32 2, 4, 8, 16 columns 159 / 147, 147 / 167, 209 / 233, 452 / 353; pf 4+6 FP64 1, 4, 8
+  // columns 15.1 / 16.6, 20.4 / 23.2, 44.3 / 32.8; pf 3+6 FP64 1, 4 columns 3.64 / 3.40, 4.53 / 4.87; pf 5+5, sectors of
+  // up to 1,651 states, FP64 1, 4 columns 27.4 / 20.6, 26.9 / 26.9).
+  if (m.pn.batches.size() > 1 && m.max_dn > 2048 && !m.pn.force && row <= 32 && (nb & (nb - 1)) == 0 &&
+      nb >= (sizeof(T) == 8 ? 1 : 4))
+    own = false;
   a.own = own ? 1 : 0;
   if (!own) {
     dispatch_hv<T>(a, P, s, 3, ~0u);

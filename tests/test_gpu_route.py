@@ -43,3 +43,27 @@ def test_route_by_space_and_row(case):
             W = {env: g.apply(x) for env, g in models.items()}
             assert not torch.equal(W["0"], W["2"])  # the two sides add in different orders
             assert torch.equal(W[""], W["2" if row in tiles else "0"]), (dt, row)
+
+
+@pytest.mark.parametrize("n", [5, 6])  # sectors of up to 1,651 and 3,952 states
+def test_narrow_rows_of_wide_sectors(n):
+    """Several batches and sectors of more than 2,048 neutron states: jump lists for rows of up to 32 bytes at widths of
+    a power of two (FP32 from 4 columns on), pair blocks beyond."""
+    tb, spe = random_tbme(PF_ORBITS, 5), [0.3 * k for k in range(4)]
+    models = {}
+    for env in ("", "0"):
+        os.environ["TRBL_PN_BATCH"] = "2000000"
+        if env:
+            os.environ["TRBL_PN_TILES"] = env
+        try:
+            models[env] = trbl.Model(PF_ORBITS, 2, n, n % 2)
+            models[env].set_hamiltonian(spe, spe, tb)
+        finally:
+            os.environ.pop("TRBL_PN_TILES", None)
+            os.environ.pop("TRBL_PN_BATCH", None)
+    V = torch.randn((models[""].dim, 8), dtype=torch.float64, generator=torch.Generator().manual_seed(1))
+    for dt, lists in ((torch.float64, (1, 2, 4)), (torch.float32, (4, 8))):
+        for nb in (1, 2, 3, 4, 5, 8):
+            say("case", dt, nb)
+            x = V[:, :nb].contiguous().to("cuda", dt)
+            assert torch.equal(models[""].apply(x), models["0"].apply(x)) == (n == 6 and nb in lists), (dt, nb)
