@@ -203,7 +203,8 @@ struct FlyCores {
 
 // One work item: up to PN_TPB cores of one (2M, parity) group and one pair block, which is laid out as the
 // matrix instructions read it (one conflict-free LDS read per fragment). Blocks of up to 16, 32 and 64
-// pairs are launches of their own: registers and LDS of the narrow ones allow 8, 5 and 4 workgroups a CU.
+// pairs are launches of their own: registers and LDS of the narrow ones allow 8, 5 and 4 workgroups a CU (64 pairs with
+// eight cores a turn, FP64 up to 4 columns: 3 by their LDS, 2 beyond 48 pairs).
 // 112Sn-like space (D = 6,210,638, 53.8 M cores of 7.5 allowed pairs on average; ms per product): 8 columns
 // FP64 38.0 -> 21.1, 1 column 32.4 -> 8.8, 16 columns 82.0 -> 44.0, 16 columns FP32 64.4 -> 21.7. (Before,
 // each core compacted its allowed pairs: 114 instructions a core and block elements gathered from LDS; in

@@ -13,9 +13,12 @@
 // Each term is counted in exactly one core pair (the core is the set of spectator nucleons;
 // a = c is a proton number operator, and its core is the target minus a), so the pn part of W is
 //   W[t] += sum over the n_prot * n_neut core pairs of t of  s_t (H_M (s V))[t].
-// A wavefront takes one core pair: it lists the allowed pairs with a ballot, gathers the source
-// rows (16 columns, or 32 in FP32: one 128-byte line each) with their signs, multiplies by the block
-// of H_M on the matrix cores, and writes each target row into a slot of its own.
+// A work item fixes one core (of protons, or of neutrons where their runs are short) and runs over cores of the
+// other species. The pair states that the fixed core leaves free are compacted once, by a ballot, and the block of H_M
+// over them is laid out in LDS as the matrix instructions read it. Several cores of the run share the 16 columns of an
+// instruction, a lane serving one core and up to 16 bytes of adjacent columns: it gathers the source rows with their
+// signs and writes each target row into a slot of its own; pairs that the run's core blocks read zeros and write
+// nothing.
 //
 // Slots. The proton cores are worked through in batches. A batch owns a slot row for every
 // (core K_p, x, position of u in the target's neutron word, target neutron state), so each slot is
@@ -300,6 +303,9 @@ struct CorePairs {
 // over them is laid out as the matrix instructions read it (one conflict-free LDS read per fragment). The cores
 // of the run then only mask sources and targets: their blocked pairs read zeros and write nothing. The first
 // workgroups of a launch add the previous batch.
+// Registers allow 4 workgroups a CU. LDS, sized for the widest block of the space, allows 3 or 4 at two and four cores
+// a turn and 2 or 3 at eight (FP64 up to 4 columns, FP32 from 4 to 8): the lists of eight cores take 32 KB, the
+// fragments of a block of 60 pairs 32 KB in FP64.
 template <class T, int VPL, int KN, bool BIG>
 __global__ __launch_bounds__(256, 4) void pn_tile_kernel(PNTileArgs<T> a) {
 #if defined(__HIP_DEVICE_COMPILE__)
