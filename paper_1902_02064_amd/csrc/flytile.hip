@@ -208,8 +208,8 @@ struct FlyCores {
 // 112Sn-like space (D = 6,210,638, 53.8 M cores of 7.5 allowed pairs on average; ms per product): 8 columns
 // FP64 38.0 -> 21.1, 1 column 32.4 -> 8.8, 16 columns 82.0 -> 44.0, 16 columns FP32 64.4 -> 21.7. (Before,
 // each core compacted its allowed pairs: 114 instructions a core and block elements gathered from LDS; in
-// one launch 25.7.) At 8 columns FP64 the slots are 26 GB written and read back; the matrix cores are busy
-// 40 % and the vector units 20 % of the kernel, the rest waits for rows.
+// one launch 25.7.) At 8 columns FP64 the slots are 27 GB written and read back and 28 GB of rows come from
+// beyond the L2; the matrix cores are busy 35 % and the vector units 20 % of the kernel, the rest waits for rows.
 template <class T, int VPL, int KN, int LP>
 __global__ __launch_bounds__(256, LP == 16 ? 8 : LP == 32 ? 5 : 4) void fly_tile_kernel(FlyTileArgs<T> a) {
 #if defined(__HIP_DEVICE_COMPILE__)

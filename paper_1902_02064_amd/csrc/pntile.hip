@@ -580,7 +580,7 @@ void build_pn_tiles(Model& m) {
   // `chunk` at a time. An item's set-up, and the lanes of a matrix instruction that the cores share, pay for
   // runs of some cores, so with one batch the items run over the protons where they would hold fewer than 4
   // neutron cores on average and the proton runs are longer (ms, over neutrons / protons, FP64 8 and 32 columns: pf
-  // 4+2 0.148 / 0.100, 0.408 / 0.305; pf 5+1 0.175 / 0.129, 0.280 / 0.210; pf 3+2 0.068 / 0.063, 0.141 / 0.132; the
+  // 4+2 0.148 / 0.099, 0.408 / 0.306; pf 5+1 0.175 / 0.139, 0.280 / 0.203; pf 3+2 0.068 / 0.064, 0.141 / 0.124; the
   // other way round pf 2+4 0.106 / 0.169, 0.288 / 0.391). TRBL_PN_RUN=p or n: a testing override.
   auto count_items = [&](bool sw, int ch) {
     int64_t n = 0;
